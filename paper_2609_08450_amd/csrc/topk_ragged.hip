@@ -105,9 +105,11 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 // k * kViewHistBytes.  Every field and entry is written and read with
 // agent-scope atomic accesses (see the arrive step).
 struct RowState {
-    uint64_t sa;         // entries reserved in the candidate buffer (low 32
-                         // bits) | segments done with Phase 2 << 32: the last
-                         // arrival's atomic returns the final reserved count
+    uint64_t sa;         // entries reserved in the candidate buffer (low 20
+                         // bits) | reservations made << 20 | segments done
+                         // with Phase 2 << 32 | those of them that wait for
+                         // the row's verdict << 48: the last arrival's atomic
+                         // returns the final counts
     uint64_t counts;     // C(tau1) | C(tau0) << 32 of the row (exact)
     uint32_t taus;       // segment 0's tau0 | tau1 << 16 | 1 << 31 once known
     uint32_t incomplete; // a segment could not keep all of its A(tau1): with
@@ -115,15 +117,22 @@ struct RowState {
                          // segments (each adds its coarse histogram)
     uint32_t amax;       // largest ascending key among the stored entries
     uint32_t varrive;    // segments that have added their part of a shared view
+    // (in a cache line of its own: waiting segments poll xtau while others
+    // still arrive)
     // The split exact route (segments that added a histogram wait for the
     // finisher's tau_star, classify their own ranges and arrive again):
-    uint32_t ocnt;       // outputs reserved (entries with c < tau_star)
+    alignas(128) uint32_t ocnt; // outputs reserved (entries with c < tau_star)
     uint32_t qcnt;       // kept entries (c == tau_star) reserved in the candidate buffer
     uint32_t arrive2;    // second arrivals
     uint64_t xtau;       // the route word: tau_star | arrivals expected << 11 |
                          // abandoned << 30 | 1 << 31 | |Q0| << 32 | |E0| << 48
     uint64_t xmask;      // segments that stopped waiting
+    // The team exact route (every member of a row's team adds a histogram,
+    // waits for the others, and selects in its own range):
+    uint64_t team;       // arrivals at the rounds' barriers | abandoned << 32
+    uint64_t tslots;     // outputs reserved | kept entries reserved << 32
 };
+static_assert(sizeof(RowState) <= kRowStateBytes, "row state fits its padding");
 
 // Workspace header (first kHeaderBytes of the workspace).
 struct WsHeader {
@@ -134,6 +143,9 @@ struct WsHeader {
     uint32_t pad[12];
     uint32_t stats[16]; // [0..5] routes, [6] reread, [7] wait fallback, [8] errors
 };
+
+constexpr uint32_t kReserved = 1u << 20; // one reservation in RowState::sa
+static_assert(kMaxSplit * kFront < (int)kReserved, "a row's reservations fit their field");
 
 enum { kStatReread = 6, kStatWaitFallback = 7, kStatErrors = 8 };
 
@@ -412,6 +424,9 @@ struct alignas(16) Smem {
     uint64_t xword;       // split exact route: a route word
 };
 
+// The workgroup's LDS state, in one place for the kernels and what they share.
+__shared__ Smem g_sm;
+
 __device__ __forceinline__ void clear_hist(Smem &sm) {
     uint4 *h4 = reinterpret_cast<uint4 *>(sm.hist);
     for (int i = threadIdx.x; i < kBins / 4; i += kBlock) h4[i] = make_uint4(0, 0, 0, 0);
@@ -528,26 +543,9 @@ __device__ __forceinline__ void stream_row(const float *scores, int64_t off, int
     }
 }
 
-// Largest range resident_row takes, in chunks.
+// Largest range that the exact route keeps in registers, in chunks (two
+// register chunks).
 constexpr int kResidentChunks = 2;
-
-// A range of at most kResidentChunks chunks held in registers: both chunks
-// are loaded once and passed to fn1, then mid() runs (every thread, may
-// synchronise), then the same registers are passed to fn2 -- a two-pass
-// computation that reads the range from memory once.
-template <class F1, class M, class F2>
-__device__ __forceinline__ void resident_row(const RowVecs &g, int32_t beg, int32_t end, F1 &&fn1,
-                                             M &&mid, F2 &&fn2) {
-    static_assert(kResidentChunks == 2, "two register chunks");
-    f4 xa[kVec], xb[kVec];
-    issue_chunk<false>(g, xa, 0);
-    issue_chunk<false>(g, xb, 1);
-    consume_chunk(g, xa, 0, beg, end, fn1);
-    consume_chunk(g, xb, 1, beg, end, fn1);
-    mid();
-    consume_chunk(g, xa, 0, beg, end, fn2);
-    consume_chunk(g, xb, 1, beg, end, fn2);
-}
 
 __device__ __forceinline__ bool in_window(int32_t i, int32_t lo, int32_t hi) {
     return i >= lo && i < hi;
@@ -762,14 +760,6 @@ __device__ __forceinline__ void count_range(Smem &sm, const float *scores, int64
 }
 
 // ----------------------------------------------------------- outputs ----
-
-__device__ __forceinline__ void emit(const KArgs a, int r, uint32_t pos, uint32_t idx,
-                                     uint32_t kappa) {
-    if (pos >= (uint32_t)a.K) return; // never taken for a consistent selection
-    const int64_t o = (int64_t)r * a.K + pos;
-    a.out_idx[o] = (int32_t)idx;
-    a.out_val[o] = __builtin_bit_cast(float, bits_from_asc(~kappa));
-}
 
 __device__ __forceinline__ void write_direct(const KArgs a, int r, const float *row, int64_t L) {
     for (int j = threadIdx.x; j < a.K; j += kBlock) {
@@ -1213,120 +1203,14 @@ __device__ __forceinline__ void refine(const KArgs a, Smem &sm, int r, bool segm
             ? refine_round<true>(a, sm, beg, end, raw, out0, placed, win, n_live, k, par)
             : refine_round<false>(a, sm, beg, end, raw, out0, placed, win, n_live, k, par);
         rounds_run++;
-        if (done) break;
+        // (distinct composite keys of 64 bits: at most seven rounds)
+        if (done || rounds_run >= 8) break;
     }
     PHASE_WORD(a, 15, (uint64_t)rounds_run);
     __syncthreads();
 }
 
 // ------------------------------------------------------ exact routes ----
-
-// Resolves an exact boundary bin that exceeds the frontier capacity without
-// materialising it; every pass re-reads the row.  The bin is a contiguous
-// range of ascending FP32 keys, [bin_cutoff(t*), bin_cutoff(t* - 1) - 1].
-// Digit rounds narrow a window on the key, largest keys first, until the
-// k-th largest key uT of the bin is known; when more elements hold uT than
-// are still needed, rounds over the row index narrow a window on the index,
-// lowest first (the composite order (kappa32, index)).  A last pass commits
-// every bin element above uT and those at uT with index <= iT.  A pass costs
-// a range test per element; only elements inside the window go further.
-__device__ __forceinline__ void reread_select(const KArgs a, Smem &sm, int r, int64_t off, int64_t L,
-                              uint32_t tstar, uint32_t k) {
-    const int tid = threadIdx.x;
-    const float *scores = a.scores;
-    const int32_t n = (int32_t)L;
-    const uint32_t bhi = tstar == 0u ? 0xFFFFFFFFu : bin_cutoff(tstar - 1u) - 1u;
-    uint32_t wlo = bin_cutoff(tstar), whi = bhi;  // key window
-    uint32_t ilo = 0u, ihi = (uint32_t)(n - 1);   // index window at key uT
-    uint32_t uT = wlo, iT = 0xFFFFFFFFu;
-    bool by_key = wlo != whi;
-    // every round narrows its window to fewer than 2^11 parts of it, so the
-    // key takes at most three rounds and the index three more
-    for (int round = 0; round < 6; round++) {
-        const uint32_t span = by_key ? whi - wlo : ihi - ilo;
-        if (span == 0u) break;                     // one key / one index left
-        const int s = max(0, 21 - (int)__builtin_clz(span)); // span >> s < 2^11
-        clear_hist(sm);
-        __syncthreads();
-        if (by_key) {
-            stream_row<false>(scores, off, 0, n, [&](const f4 *x, const int32_t *i0, int32_t lo,
-                                                     int32_t hi, bool edge, int32_t mv) {
-#pragma unroll
-                for (int m = 0; m < kVec; m++) if (m < mv) {
-#pragma unroll
-                    for (int c = 0; c < 4; c++) {
-                        const uint32_t u = asc_key(fbits(x[m][c]));
-                        if (u - wlo <= span && (!edge || in_window(i0[m] + c, lo, hi)))
-                            atomicAdd(&sm.hist[(whi - u) >> s], 1u);
-                    }
-                }
-            });
-        } else {
-            stream_row<false>(scores, off, 0, n, [&](const f4 *x, const int32_t *i0, int32_t lo,
-                                                     int32_t hi, bool edge, int32_t mv) {
-#pragma unroll
-                for (int m = 0; m < kVec; m++) if (m < mv) {
-#pragma unroll
-                    for (int c = 0; c < 4; c++) {
-                        const uint32_t u = asc_key(fbits(x[m][c]));
-                        const uint32_t di = (uint32_t)(i0[m] + c) - ilo;
-                        if (u == uT && di <= span && (!edge || in_window(i0[m] + c, lo, hi)))
-                            atomicAdd(&sm.hist[di >> s], 1u);
-                    }
-                }
-            });
-        }
-        __syncthreads();
-        if (tid < 64) wave_find(sm.hist, k, 0, 1, sm.find);
-        __syncthreads();
-        const Find f = sm.find[0];
-        __syncthreads();
-        const uint32_t need = k - f.below;
-        if (by_key) {
-            // digit b holds keys whi - u in [b << s, (b + 1) << s)
-            const uint64_t b0 = (uint64_t)f.bin << s, b1 = ((uint64_t)f.bin + 1u) << s;
-            const uint32_t nlo = b1 > (uint64_t)span ? wlo : whi - (uint32_t)(b1 - 1u);
-            whi = whi - (uint32_t)b0;
-            wlo = nlo;
-            uT = wlo;
-            if (f.eq == need) break;               // the whole digit is taken
-            by_key = wlo != whi;                   // else ties at uT: index rounds
-        } else {
-            ilo += f.bin << s;
-            ihi = min(ihi, ilo + ((1u << s) - 1u));
-            iT = ihi;
-            if (f.eq == need) break;
-        }
-        k = need;
-    }
-    // Output pass: bin elements with key above uT, and those at uT with index <= iT.
-    const uint32_t tspan = bhi - uT;
-    stream_row<false>(scores, off, 0, n, [&](const f4 *x, const int32_t *i0, int32_t lo,
-                                             int32_t hi, bool edge, int32_t mv) {
-#pragma unroll
-        for (int m = 0; m < kVec; m++) if (m < mv) {
-#pragma unroll
-            for (int c = 0; c < 4; c++) {
-                const uint32_t u = asc_key(fbits(x[m][c]));
-                const int32_t i = i0[m] + c;
-                const bool sel = u - uT <= tspan && (u != uT || (uint32_t)i <= iT) &&
-                                 (!edge || in_window(i, lo, hi));
-                const uint64_t em = __ballot(sel);
-                if (em == 0) continue;
-                // one position claim per wave (the output order is free)
-                const int lead = __builtin_ctzll(em);
-                uint32_t op = 0u;
-                if (lane_id() == lead) op = atomicAdd(&sm.opos, (uint32_t)__popcll(em));
-                op = __builtin_amdgcn_readlane(op, lead);
-                if (sel)
-                    emit(a, r, op + __builtin_amdgcn_mbcnt_hi((uint32_t)(em >> 32),
-                                         __builtin_amdgcn_mbcnt_lo((uint32_t)em, 0u)),
-                         (uint32_t)i, ~u);
-            }
-        }
-    });
-    __syncthreads();
-}
 
 // Coarse bins of one streamed chunk added into sm.hist.
 __device__ __forceinline__ void coarse_hist_chunk(Smem &sm, const f4 *x, const int32_t *i0,
@@ -1369,131 +1253,471 @@ __device__ __forceinline__ void hist_counts(Smem &sm, uint32_t b0, uint32_t b1) 
     __syncthreads();
 }
 
-// Exact coarse recovery (eq:method:exact-init) over the whole row by this
-// workgroup: a coarse histogram pass finds tau_star = min{b : C(b) >= K}; a
-// classify pass commits c < tau_star to the output (E0) and keeps
-// c == tau_star as the frontier Q0 when it fits the capacity.  A row of at
-// most kResidentChunks chunks is read once and both passes run from
-// registers; a longer one is streamed twice.  Returns (tau_star, |E0|, |Q0|)
-// in sm.find[0]; ends with a barrier, sm.hist cleared.  With have_hist the
-// coarse histogram is already in sm.hist (exact_hist) and only the classify
-// pass runs.
-__device__ __forceinline__ void exact_classify(const KArgs a, Smem &sm, int r, int64_t off, int64_t L,
-                                               bool have_hist) {
-    const int tid = threadIdx.x;
-    auto hist = [&](const f4 *x, const int32_t *i0, int32_t lo, int32_t hi, bool edge,
-                    int32_t mv) { coarse_hist_chunk(sm, x, i0, lo, hi, edge, mv); };
-    // After the find: c < tau_star iff u >= key_hi, c == tau_star iff
-    // key_lo <= u < key_hi (the bins' ascending-key endpoints); an empty
-    // keep range when the bin does not fit the frontier.  When E0 and Q0 fit
-    // the LDS pairs together, E0 is staged at their top (e0_top on) and
-    // written out after the pass, so that the pass itself stores nothing to
-    // global memory (a store in the loop would make each wait for the next
-    // chunk's loads wait for the stores as well).
-    uint32_t key_lo = 0, key_hi = 0, e0_top = kFront, below = 0;
-    bool stage = false;
-    auto find = [&]() {
-        PHASE_MARK(a, 22);
-        __syncthreads();
-        PHASE_MARK(a, 23);
-        if (tid < 64) wave_find(sm.hist, (uint32_t)a.K, 0, 1, sm.find);
-        if (tid == 0) sm.cnt = 0;
-        __syncthreads();
-        PHASE_MARK(a, 24);
-        const uint32_t tstar = sm.find[0].bin;
-        const bool fits = sm.find[0].eq <= (uint32_t)a.cap;
-        key_hi = tstar > 0 ? bin_cutoff(tstar - 1) : 0xFFFFFFFFu;
-        key_lo = fits ? bin_cutoff(tstar) : key_hi;
-        below = sm.find[0].below;
-        stage = below + (fits ? sm.find[0].eq : 0u) <= (uint32_t)kFront;
-        e0_top = (uint32_t)kFront - below;
-    };
-    // Appends are wave-aggregated per chunk: each lane builds bit masks of
-    // its committed and kept elements, a wave scan of the two counts (packed
-    // in one word: at most 16 per lane) gives each lane its first slots, and
-    // lane 0 reserves the wave's total with one LDS atomic per category.
-    static_assert(kVec * 4 <= 16 && kWaves * 64 * 16 < 65536, "packed counts");
-    const int lane = lane_id();
-    int32_t *oi = a.out_idx + (int64_t)r * a.K;
-    float *ov = a.out_val + (int64_t)r * a.K;
-    auto classify = [&](const f4 *x, const int32_t *i0, int32_t lo, int32_t hi, bool edge,
-                        int32_t mv) {
-        uint32_t mlt = 0, meq = 0;
-#pragma unroll
-        for (int m = 0; m < kVec; m++) if (m < mv) {
-#pragma unroll
-            for (int c = 0; c < 4; c++) {
-                const uint32_t u = asc_key(fbits(x[m][c]));
-                const bool in = !edge || in_window(i0[m] + c, lo, hi);
-                mlt |= (in && u >= key_hi ? 1u : 0u) << (m * 4 + c);
-                meq |= (in && u >= key_lo && u < key_hi ? 1u : 0u) << (m * 4 + c);
+// ------------------------------------------------- team exact route ----
+//
+// Exact selection of a row without a sampled proposal (eq:method:exact-init,
+// then Section 4.4's refinement), by one workgroup or by a team of T of them,
+// member t taking the t-th part of the row.  Rounds of histograms narrow a
+// window that holds the K-th entry: first over coarse bins (which gives
+// tau_star and |Q0|), then, while the window holds more entries than the
+// frontier, over digits of the key and last of the row index (the composite
+// order).  One pass then writes every entry above the window to the output and
+// keeps the window's entries, which the last member refines.  A range of at
+// most kResidentChunks chunks is loaded into registers once and every pass
+// runs from them; a longer one is streamed for each pass.
+//
+// A team's members add their histograms into one of the row (agent-scope
+// atomics), arrive on a counter and wait until all T have, and each finds the
+// same window in the merged histogram.  The wait is bounded as the boundary
+// wait is (a member may not be running yet while another kernel holds the
+// GPU): a member that stops waiting marks the row abandoned, which it can do
+// only while the round is incomplete, so that either every member passes the
+// last round or none does.  The last member to leave an abandoned row runs it
+// alone.
+//
+// Both passes are bound by vector instructions, not by loads (a workgroup
+// has a CU's four SIMDs at best), hence the raw FP16 bins (three instructions
+// an element instead of six) and an append of about eight (below), where
+// per-lane bit masks placed by a scan took about 35.
+
+constexpr uint64_t kAbandoned = 1ull << 32; // in RowState::team
+constexpr uint32_t kSoloKeep = 1024; // most kept entries of a lone workgroup (hist2 holds them)
+
+struct TeamResult {
+    uint32_t tstar, eq; // tau_star and |Q0| of the row
+    bool done;          // this member finished the row
+    bool alone;         // the team gave up, and this member has to run the row alone
+};
+
+// Bin of the raw FP16 pattern: the coarse bins in another order, which
+// raw_bin_of undoes (c < 1024: non-negative patterns, descending).
+__device__ __forceinline__ uint32_t raw_bin(float x) {
+    return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)x) >> 5;
+}
+__device__ __forceinline__ uint32_t raw_bin_of(uint32_t c) { return c < 1024u ? 1023u - c : c; }
+
+// The thread's four bins of a histogram (4 tid ..) summed into 64 group sums
+// of 32 bins each (complete after the next barrier).
+__device__ __forceinline__ void group_sums_of(const uint4 &h, uint32_t *out) {
+    uint32_t v = h.x + h.y + h.z + h.w;
+    v += __builtin_amdgcn_update_dpp(0u, v, 0x111, 0xf, 0xf, false); // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0u, v, 0x112, 0xf, 0xf, false); // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0u, v, 0x114, 0xf, 0xf, false); // row_shr:4
+    if ((threadIdx.x & 7u) == 7u) out[threadIdx.x >> 3] = v;
+}
+
+// min{b : H(b) >= k} with its counts, by every wave on its own; groups: the
+// 64 group sums.  raw: hist and groups are in raw FP16 order.
+__device__ __forceinline__ Find find_bin(const uint32_t *hist, const uint32_t *groups, uint32_t k,
+                                         bool raw) {
+    const uint32_t lane = (uint32_t)lane_id();
+    const uint32_t c = groups[raw && lane < 32u ? 31u - lane : lane];
+    const uint32_t incl = wave_incl_scan(c);
+    const uint32_t total = __builtin_amdgcn_readlane(incl, 63);
+    Find f;
+    if (k == 0 || k > total) {
+        f.bin = kBins; f.below = total; f.eq = 0;
+        return f;
+    }
+    const uint32_t owner = (uint32_t)__ffsll((unsigned long long)__ballot(incl >= k)) - 1u;
+    const uint32_t base = __builtin_amdgcn_readlane(incl - c, owner);
+    const uint32_t b = owner * 32u + (lane & 31u);
+    const uint32_t v = lane < 32u ? hist[raw ? raw_bin_of(b) : b] : 0u;
+    const uint32_t incl2 = wave_incl_scan(v);
+    const int l2 = __ffsll((unsigned long long)__ballot(lane < 32u && base + incl2 >= k)) - 1;
+    f.bin = owner * 32u + (uint32_t)l2;
+    f.below = base + __builtin_amdgcn_readlane(incl2 - v, l2);
+    f.eq = __builtin_amdgcn_readlane(v, l2);
+    return f;
+}
+
+// Entries of a histogram in bins below `bin`, and in it (one wave; uniform).
+__device__ __forceinline__ uint2 bin_counts(const uint32_t *hist, const uint32_t *groups,
+                                            uint32_t bin, bool raw) {
+    const uint32_t lane = (uint32_t)lane_id(), owner = bin >> 5;
+    uint32_t c = lane < owner ? groups[raw && lane < 32u ? 31u - lane : lane] : 0u;
+    const uint32_t b = owner * 32u + (lane & 31u);
+    const uint32_t v = lane < 32u ? hist[raw ? raw_bin_of(b) : b] : 0u;
+    c += lane < (bin & 31u) ? v : 0u;
+    return make_uint2(__builtin_amdgcn_readlane(wave_incl_scan(c), 63),
+                      __builtin_amdgcn_readlane(v, bin & 31u));
+}
+
+// Adds a thread's bins [4 tid, 4 tid + 4) into a row's histogram.
+__device__ __forceinline__ void add_bins(uint32_t *d, const uint4 &h) {
+    if (h.x) __hip_atomic_fetch_add(d + 0, h.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (h.y) __hip_atomic_fetch_add(d + 1, h.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (h.z) __hip_atomic_fetch_add(d + 2, h.z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (h.w) __hip_atomic_fetch_add(d + 3, h.w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void zero_bins(uint32_t *d) {
+    uint64_t *p = reinterpret_cast<uint64_t *>(d);
+    __hip_atomic_store(p, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A member's arrival at a round's barrier and its wait for the others (thread
+// 0); target: arrivals that complete the round.  Returns whether it passed.
+__device__ __forceinline__ bool team_arrive(const KArgs &a, RowState *rs, uint32_t target) {
+    uint64_t v = 1ull + __hip_atomic_fetch_add(&rs->team, 1ull, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t t_wait = wall_clock64();
+    int spin = 0;
+    while (!(v & kAbandoned) && (uint32_t)v < target) {
+        if (spin++ >= a.spin_limit || wall_clock64() - t_wait > a.spin_ticks) {
+            // (fails, with v reloaded, when another member arrived meanwhile)
+            if (__hip_atomic_compare_exchange_strong(&rs->team, &v, v | kAbandoned,
+                                                     __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT)) {
+                atomicAdd(&a.hdr->stats[kStatWaitFallback], 1u);
+                return false;
             }
+            continue;
         }
-        const uint32_t packed = (uint32_t)__popc(mlt) | ((uint32_t)__popc(meq) << 16);
-        const uint32_t incl = wave_incl_scan(packed);
-        const uint32_t tot = __builtin_amdgcn_readlane(incl, 63);
-        if (tot == 0) return;
-        uint32_t bl = 0, be = 0;
-        if (lane == 0) {
-            if (tot & 0xFFFFu) bl = atomicAdd(&sm.opos, tot & 0xFFFFu);
-            if (tot >> 16) be = atomicAdd(&sm.cnt, tot >> 16);
+        __builtin_amdgcn_s_sleep(1);
+        v = __hip_atomic_load(&rs->team, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return !(v & kAbandoned);
+}
+
+// The last member's: the team's part of the row state, and its histograms.
+__device__ __forceinline__ void team_reset(RowState *rs, uint32_t *vh, uint32_t *xh) {
+    zero_bins(vh + 4 * threadIdx.x);
+    zero_bins(xh + 4 * threadIdx.x);
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(&rs->team, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&rs->tslots, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&rs->arrive2, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// Row elements [beg, end) of member t of T (kTeam: T > 1, with the row's
+// state rs, histograms vh and xh (zero) and candidate buffer gc).  have_hist:
+// the row's coarse histogram is already in sm.hist (a lone workgroup).
+// Otherwise sm.hist need not be clear.  Every output of the row is written
+// once the member with `done` returns; after an abandoned round the last member
+// to leave gets `alone` instead, and runs the whole row (the others are done
+// with it).  Ends with a barrier.
+template <bool kTeam>
+__device__ __forceinline__ TeamResult exact_select(const KArgs a, Smem &sm, int r, int64_t off,
+                                                   int64_t L, int32_t beg, int32_t end, int T,
+                                                   int t, RowState *rs, uint32_t *vh,
+                                                   uint32_t *xh, uint64_t *gc, bool have_hist) {
+    const int tid = threadIdx.x;
+    const uint32_t lane = (uint32_t)lane_id(), w8 = (uint32_t)tid >> 6;
+    const uint32_t K = (uint32_t)a.K;
+    const RowVecs g = row_vecs(a.scores, off, beg, end);
+    const bool resident = g.nch <= kResidentChunks;
+    f4 xa[kVec], xb[kVec];
+    if (resident) {
+        issue_chunk<false>(g, xa, 0);
+        issue_chunk<false>(g, xb, 1);
+    }
+    // fn over every chunk.  One rolled loop serves both forms, the next chunk
+    // in flight while one is consumed when it streams: a body for each
+    // register chunk made the compiler keep the keys and window masks of one
+    // pass for the next (128 VGPRs and spills).
+    auto pass = [&](auto &&fn) {
+        if (!resident) issue_chunk<false>(g, xa, 0);
+#pragma nounroll
+        for (int32_t c = 0; c < g.nch; c++) {
+            f4 x[kVec];
+            if (resident && c) {
+#pragma unroll
+                for (int m = 0; m < kVec; m++) x[m] = xb[m];
+            } else {
+#pragma unroll
+                for (int m = 0; m < kVec; m++) x[m] = xa[m];
+            }
+            if (!resident) issue_chunk<false>(g, xa, c + 1);
+            consume_chunk(g, x, c, beg, end, fn);
         }
-        const uint32_t excl = incl - packed;
-        const uint32_t pl0 = __builtin_amdgcn_readfirstlane(bl) + (excl & 0xFFFFu);
-        const uint32_t pe0 = __builtin_amdgcn_readfirstlane(be) + (excl >> 16);
-        // slot of the element at bit b: the first slot plus the hits below b
-        auto write = [&](auto staged) {
-            constexpr bool kStaged = decltype(staged)::value;
+    };
+    // the third histogram of a team's row: the candidate buffer past the
+    // entries that can be kept
+    uint32_t *const gb[3] = {vh, xh, kTeam ? reinterpret_cast<uint32_t *>(gc + kCap) : nullptr};
+    static_assert((size_t)(kFront - kCap) * sizeof(uint64_t) >= kViewHistBytes, "room for bins");
+
+    // the window: keys [wlo, whi], row indices [ilo, ihi] (the latter narrowed
+    // only once one key is left)
+    uint32_t wlo = 0u, whi = ~0u, ilo = 0u, ihi = ~0u;
+    uint32_t below = 0, eq = 0, own_lt = 0, own_eq = 0;
+    bool by_key = true, take_all = false;
+    int shift = 0;
+    TeamResult res;
+    res.tstar = 0; res.eq = 0; res.done = false; res.alone = false;
+    bool passed = true;
+    int round = 0;
+    for (;; round++) {
+        if (round || !have_hist) {
+            if (round) __syncthreads(); // the last round's bins have been read
+            clear_hist(sm);
+            __syncthreads();
+            if (round == 0) {
+                pass([&](const f4 *x, const int32_t *i0, int32_t lo, int32_t hi, bool edge,
+                         int32_t mv) {
 #pragma unroll
-            for (int m = 0; m < kVec; m++) if (m < mv) {
+                    for (int m = 0; m < kVec; m++) if (m < mv) {
+                        if (edge) {
 #pragma unroll
-                for (int c = 0; c < 4; c++) {
-                    const int b = m * 4 + c;
-                    const uint32_t below_b = (1u << b) - 1u;
-                    const uint32_t i = (uint32_t)(i0[m] + c);
-                    if ((mlt >> b) & 1u) {
-                        const uint32_t pl = pl0 + (uint32_t)__popc(mlt & below_b);
-                        if constexpr (kStaged) {
-                            sm.ci[e0_top + pl] = i; // pl < below: inside the top
-                            sm.ck[e0_top + pl] = fbits(x[m][c]);
-                        } else if (pl < (uint32_t)a.K) { // never false for a consistent selection
-                            oi[pl] = (int32_t)i;
-                            ov[pl] = x[m][c];
+                            for (int c = 0; c < 4; c++)
+                                if (in_window(i0[m] + c, lo, hi))
+                                    atomicAdd(&sm.hist[raw_bin(x[m][c])], 1u);
+                        } else {
+#pragma unroll
+                            for (int c = 0; c < 4; c++) atomicAdd(&sm.hist[raw_bin(x[m][c])], 1u);
                         }
                     }
-                    if ((meq >> b) & 1u) {
-                        const uint32_t pe = pe0 + (uint32_t)__popc(meq & below_b);
-                        sm.ci[pe] = i;
-                        sm.ck[pe] = ~asc_key(fbits(x[m][c]));
+                });
+            } else {
+                const uint32_t kspan = whi - wlo, ispan = by_key ? ~0u : ihi - ilo;
+                pass([&](const f4 *x, const int32_t *i0, int32_t lo, int32_t hi, bool edge,
+                         int32_t mv) {
+#pragma unroll
+                    for (int m = 0; m < kVec; m++) if (m < mv) {
+#pragma unroll
+                        for (int c = 0; c < 4; c++) {
+                            const uint32_t u = asc_key(fbits(x[m][c]));
+                            const uint32_t di = (uint32_t)(i0[m] + c) - ilo;
+                            if (u - wlo <= kspan && (by_key || di <= ispan) &&
+                                (!edge || in_window(i0[m] + c, lo, hi)))
+                                atomicAdd(&sm.hist[(by_key ? whi - u : di) >> shift], 1u);
+                        }
+                    }
+                });
+            }
+        }
+        const bool raw = round == 0 && !have_hist;
+        __syncthreads();
+        PHASE_MARK(a, 21);
+        const uint4 h = reinterpret_cast<const uint4 *>(sm.hist)[tid];
+        group_sums_of(h, sm.coarse[0]);
+        const uint32_t *H = sm.hist, *G = sm.coarse[0];
+        if constexpr (kTeam) {
+            uint32_t *d = gb[round % 3] + 4 * tid;
+            add_bins(d, h);
+            // member 0 clears the histogram of the round after next (the
+            // others' first additions to it follow the next barrier); vh and
+            // xh are clear for the first two rounds
+            if (t == 0 && round >= 1) zero_bins(gb[(round + 1) % 3] + 4 * tid);
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            PHASE_MARK(a, 22);
+            if (tid == 0) sm.flag = team_arrive(a, rs, (uint32_t)(round + 1) * (uint32_t)T) ? 1u : 0u;
+            __syncthreads();
+            PHASE_MARK(a, 23);
+            passed = sm.flag != 0u;
+            if (!passed) break;
+            const uint64_t *m = reinterpret_cast<const uint64_t *>(d);
+            const uint64_t m0 = __hip_atomic_load(m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t m1 = __hip_atomic_load(m + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint4 hm = make_uint4((uint32_t)m0, (uint32_t)(m0 >> 32), (uint32_t)m1,
+                                        (uint32_t)(m1 >> 32));
+            reinterpret_cast<uint4 *>(sm.hist2)[tid] = hm;
+            group_sums_of(hm, sm.coarse[1]);
+            H = sm.hist2;
+            G = sm.coarse[1];
+        }
+        __syncthreads();
+        const uint32_t need0 = K - below;
+        const Find f = find_bin(H, G, need0, raw);
+        if constexpr (kTeam) {
+            const uint2 own = bin_counts(sm.hist, sm.coarse[0], f.bin, raw);
+            own_lt += own.x;
+            own_eq = own.y;
+        }
+        PHASE_MARK(a, 24);
+        below += f.below;
+        eq = f.eq;
+        take_all = f.eq == need0 - f.below;
+        if (round == 0) {
+            res.tstar = f.bin;
+            res.eq = f.eq;
+            whi = f.bin ? bin_cutoff(f.bin - 1u) - 1u : ~0u;
+            wlo = bin_cutoff(f.bin);
+        } else if (by_key) {
+            // digit b holds keys whi - u in [b << s, (b + 1) << s)
+            const uint64_t b0 = (uint64_t)f.bin << shift, b1 = ((uint64_t)f.bin + 1u) << shift;
+            const uint32_t nlo = b1 > (uint64_t)(whi - wlo) ? wlo : whi - (uint32_t)(b1 - 1u);
+            whi -= (uint32_t)b0;
+            wlo = nlo;
+        } else {
+            ilo += f.bin << shift;
+            ihi = min(ihi, ilo + ((1u << shift) - 1u));
+        }
+        // (every round leaves less than 2^-10 of its window, so three rounds
+        // of the key and three of the index end the search)
+        if (take_all || eq <= (kTeam ? (uint32_t)kCap : kSoloKeep) || round >= 7) break;
+        if (by_key && wlo == whi) {
+            by_key = false;
+            ihi = (uint32_t)(L - 1);
+        }
+        const uint32_t span = by_key ? whi - wlo : ihi - ilo;
+        shift = span ? max(0, 21 - (int)__builtin_clz(span)) : 0; // span >> shift < 2^11
+    }
+
+    if (passed) {
+        // Slots for this member's part of both sets, then one pass: entries at
+        // or above the window are appended to the wave's region by ballot, as
+        // in Phase 2, and a region that might not take another vector's hits
+        // is written out on the way.
+        uint32_t n_lt = below, n_eq = eq;
+        if (kTeam) { n_lt = own_lt; n_eq = own_eq; }
+        if (take_all) { n_lt += n_eq; n_eq = 0; }
+        if (tid == 0) {
+            sm.opos = 0;
+            sm.cnt = 0;
+            uint64_t s = 0;
+            if (kTeam && (n_lt | n_eq))
+                s = __hip_atomic_fetch_add(&rs->tslots, (uint64_t)n_lt | ((uint64_t)n_eq << 32),
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            sm.xword = s;
+        }
+        __syncthreads();
+        PHASE_MARK(a, 25);
+        const uint32_t e_base = (uint32_t)sm.xword, q_base = (uint32_t)(sm.xword >> 32);
+        const int64_t out0 = (int64_t)r * a.K;
+        uint32_t *wi = sm.ci + w8 * kWaveStride, *wk = sm.ck + w8 * kWaveStride;
+        uint64_t *keep = reinterpret_cast<uint64_t *>(sm.hist2); // a lone workgroup's kept entries
+        uint32_t cur = 0; // entries in the wave's region (uniform)
+        auto flush = [&]() {
+            for (uint32_t e0 = 0; e0 < cur; e0 += 64) {
+                const bool in = e0 + lane < cur;
+                const uint32_t idx = wi[e0 + lane], bits = wk[e0 + lane];
+                const uint32_t u = asc_key(bits);
+                const bool kept = in && !take_all && !(u > whi || (u == whi && idx < ilo));
+                const uint64_t ml = __ballot(in && !kept), mq = __ballot(kept);
+                uint32_t pl = 0, pq = 0;
+                if (lane == 0) {
+                    if (ml) pl = atomicAdd(&sm.opos, (uint32_t)__popcll(ml));
+                    if (mq) pq = atomicAdd(&sm.cnt, (uint32_t)__popcll(mq));
+                }
+                // (read while every lane is active: lane 0 holds them)
+                pl = __builtin_amdgcn_readfirstlane(pl);
+                pq = __builtin_amdgcn_readfirstlane(pq);
+                if (kept) {
+                    const uint32_t q = pq +
+                        __builtin_amdgcn_mbcnt_hi((uint32_t)(mq >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)mq, 0u));
+                    const uint64_t z = (uint64_t)idx | ((uint64_t)bits << 32);
+                    if (kTeam) {
+                        if (q_base + q < (uint32_t)kCap) // (never false for consistent counts)
+                            __hip_atomic_store(&gc[q_base + q], z, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                    } else if (q < kSoloKeep) {
+                        keep[q] = z;
+                    }
+                } else if (in) {
+                    const uint32_t p = e_base + pl +
+                        __builtin_amdgcn_mbcnt_hi((uint32_t)(ml >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)ml, 0u));
+                    if (p < K) put_out(a, out0, p, idx, bits); // (as above)
+                }
+            }
+            cur = 0;
+        };
+        const bool by_index = !by_key;
+        pass([&](const f4 *x, const int32_t *i0, int32_t lo, int32_t hi, bool edge, int32_t mv) {
+            auto run = [&](auto simple) {
+                // simple: a positive endpoint (x >= v iff the raw bits compare
+                // >= as signed integers), no range edge, no index window
+                constexpr bool kSimple = decltype(simple)::value;
+                const int32_t t1 = (int32_t)bits_from_asc(wlo);
+                const uint32_t dummy = (uint32_t)kWaveCap + 1u + lane;
+#pragma unroll
+                for (int m = 0; m < kVec; m++) if (m < mv) {
+                    bool hit[4];
+                    uint64_t mk[4];
+#pragma unroll
+                    for (int c = 0; c < 4; c++) {
+                        const uint32_t b = fbits(x[m][c]);
+                        if constexpr (kSimple) {
+                            hit[c] = (int32_t)b >= t1;
+                        } else {
+                            const uint32_t u = asc_key(b);
+                            const uint32_t i = (uint32_t)(i0[m] + c);
+                            hit[c] = u >= wlo && (!by_index || u > whi || i <= ihi) &&
+                                     (!edge || in_window((int32_t)i, lo, hi));
+                        }
+                        mk[c] = __ballot(hit[c]);
+                    }
+                    if (!(mk[0] | mk[1] | mk[2] | mk[3])) continue;
+                    if (cur > (uint32_t)kWaveCap - 256u) flush();
+#pragma unroll
+                    for (int c = 0; c < 4; c++) {
+                        const uint32_t q = __builtin_amdgcn_mbcnt_hi((uint32_t)(mk[c] >> 32),
+                                               __builtin_amdgcn_mbcnt_lo((uint32_t)mk[c], cur));
+                        const uint32_t d = hit[c] ? q : dummy;
+                        wi[d] = (uint32_t)(i0[m] + c);
+                        wk[d] = fbits(x[m][c]);
+                        cur += (uint32_t)__popcll(mk[c]);
+                    }
+                }
+            };
+            if (wlo > 0x80000000u && !edge && !by_index) run(std::true_type{});
+            else run(std::false_type{});
+        });
+        PHASE_MARK(a, 26);
+        flush();
+    }
+
+    uint32_t n_ref = take_all ? 0u : eq;
+    if constexpr (kTeam) {
+        // (as for a segment's candidates: every wave's accesses complete
+        // before the barrier that precedes the arrival)
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (tid == 0)
+            sm.flag = __hip_atomic_fetch_add(&rs->arrive2, 1u, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(T - 1);
+        __syncthreads();
+        PHASE_MARK(a, 27);
+        if (!sm.flag) return res;
+        // the last member: kept entries as kappa32 keys, the row's state zeroed
+        if (passed) {
+            for (uint32_t e0 = 0; e0 < n_ref; e0 += 4 * kBlock) {
+                uint64_t q[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const uint32_t e = e0 + (uint32_t)(j * kBlock + tid);
+                    q[j] = e < n_ref ? __hip_atomic_load(&gc[e], __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+                }
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const uint32_t e = e0 + (uint32_t)(j * kBlock + tid);
+                    if (e < n_ref) {
+                        sm.ci[e] = (uint32_t)q[j];
+                        sm.ck[e] = ~asc_key((uint32_t)(q[j] >> 32));
                     }
                 }
             }
-        };
-        if (stage) write(std::true_type{});
-        else write(std::false_type{});
-    };
-    const RowVecs g = row_vecs(a.scores, off, 0, (int32_t)L);
-    PHASE_MARK(a, 21);
-    if (have_hist) {
-        find();
-        stream_row<false>(a.scores, off, 0, (int32_t)L, classify);
-    } else if (g.nch <= kResidentChunks) {
-        resident_row(g, 0, (int32_t)L, hist, find, classify);
+        }
+        team_reset(rs, vh, xh);
+        if (!passed) {
+            __syncthreads();
+            res.alone = true;
+            return res;
+        }
     } else {
-        stream_row<false>(a.scores, off, 0, (int32_t)L, hist);
-        find();
-        stream_row<false>(a.scores, off, 0, (int32_t)L, classify);
-    }
-    PHASE_MARK(a, 25);
-    if (stage) {
         __syncthreads();
-        for (uint32_t e = (uint32_t)tid; e < below; e += kBlock) {
-            oi[e] = (int32_t)sm.ci[e0_top + e];
-            ov[e] = __builtin_bit_cast(float, sm.ck[e0_top + e]);
+        const uint64_t *keep = reinterpret_cast<const uint64_t *>(sm.hist2);
+        for (uint32_t e = (uint32_t)tid; e < n_ref; e += kBlock) {
+            const uint64_t z = keep[e];
+            sm.ci[e] = (uint32_t)z;
+            sm.ck[e] = ~asc_key((uint32_t)(z >> 32));
         }
     }
+    res.done = true;
     clear_hist(sm);
+    reset_range(sm);
     __syncthreads();
+    PHASE_MARK(a, 28);
+    if (n_ref)
+        refine(a, sm, r, false, n_ref, false, wlo, 0u, n_ref, K - below, (uint32_t)(L - 1));
+    PHASE_MARK(a, 29);
+    return res;
 }
 
 // -------------------------------------------------------- Phase 1 ----
@@ -1782,7 +2006,7 @@ __device__ __forceinline__ void finish_row(const KArgs a, Smem &sm, int r, int64
     const uint32_t K = (uint32_t)a.K;
     const uint32_t cap = (uint32_t)a.cap;
     int32_t trC1 = -1, tstar = -1, nq = -1;
-    uint32_t route, n_ref = 0, k_ref = K, kmin = 0;
+    uint32_t route, n_ref = 0, kmin = 0;
     if (!sampled) {
         route = TOPK_ROUTE_EXACT_UNSAMPLED;
     } else if (C0 >= K && C0 <= cap) {
@@ -1831,32 +2055,18 @@ __device__ __forceinline__ void finish_row(const KArgs a, Smem &sm, int r, int64
     // (the hint keeps this rarely taken code out of the hot path's layout;
     // measured: the decode batch runs ~1 % faster with it)
     if (__builtin_expect(exact, 0)) {
-        exact_classify(a, sm, r, off, L, have_hist);
-        const Find f = sm.find[0];
-        tstar = (int32_t)f.bin;
-        nq = (int32_t)f.eq;
-        k_ref = K - f.below;
-        if (f.eq <= cap) {
-            n_ref = f.eq;
-            f_seg = false;
-            f_raw = false;
-            f_n = f.eq;
-            // the frontier is coarse bin tau*: ascending keys from its
-            // endpoint up; the range pass measures the keys and indices
-            // present (a bin of ties then needs only index digits)
-            f_amin = bin_cutoff(f.bin);
-            f_amax = 0u;
-        } else {
-            route |= TOPK_ROUTE_REREAD_FLAG;
-            reread_select(a, sm, r, off, L, f.bin, k_ref);
-        }
+        const TeamResult x = exact_select<false>(a, sm, r, off, L, 0, (int32_t)L, 1, 0, nullptr,
+                                                 nullptr, nullptr, nullptr, have_hist);
+        tstar = (int32_t)x.tstar;
+        nq = (int32_t)x.eq;
+        if (x.eq > cap) route |= TOPK_ROUTE_REREAD_FLAG;
     }
     PHASE_MARK(a, 9);
     if (f_amax != 0u && f_amax < f_amin) f_amax = 0u;
     if (n_ref) {
         reset_range(sm);
         __syncthreads();
-        refine(a, sm, r, f_seg, f_n, f_raw, f_amin, f_amax, n_ref, k_ref, (uint32_t)(L - 1));
+        refine(a, sm, r, f_seg, f_n, f_raw, f_amin, f_amax, n_ref, K, (uint32_t)(L - 1));
     }
     PHASE_MARK(a, 13);
     if (threadIdx.x == 0) {
@@ -2328,13 +2538,170 @@ __device__ __forceinline__ bool split_exact_final(const KArgs a, Smem &sm, int r
     return true;
 }
 
+// Counts the route of a row that its team finished (in a call without an item
+// table, a proposal that failed: see finish_row) and writes its trace.
+__device__ __forceinline__ void record_team_row(const KArgs a, const Smem &sm, int r, int64_t nv,
+                                                RowState *rs, const TeamResult &x) {
+    const uint64_t cc = __hip_atomic_load(&rs->counts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t C1 = (uint32_t)cc, C0 = (uint32_t)(cc >> 32);
+    const bool under = C0 < (uint32_t)a.K, reread = x.eq > (uint32_t)a.cap;
+    const uint32_t route = under && C1 < (uint32_t)a.K ? TOPK_ROUTE_EXACT_UNDERFILL
+                                                       : TOPK_ROUTE_EXACT_OVERFLOW;
+    atomicAdd(&a.hdr->stats[route], 1u);
+    if (reread) atomicAdd(&a.hdr->stats[kStatReread], 1u);
+    if (a.trace) {
+        int32_t *w = a.trace + (int64_t)r * TOPK_TRACE_WORDS;
+        w[0] = (int32_t)(route | (reread ? TOPK_ROUTE_REREAD_FLAG : 0)); w[1] = (int32_t)nv;
+        w[2] = (int32_t)sm.tau0; w[3] = (int32_t)sm.tau1;
+        w[4] = (int32_t)C0; w[5] = under ? (int32_t)C1 : -1;
+        w[6] = (int32_t)x.tstar; w[7] = (int32_t)x.eq;
+    }
+}
+
+// What ends a row that the register finish did not: the general finish and the
+// exact route of one workgroup (finish_row), and in calls without an item
+// table a segment's wait for its row's verdict and the row's team.  It reads
+// the row's length and offset (or its table entry) again, by an index the
+// compiler cannot see through, so that they do not stay live across the hot
+// path for its sake: with the values passed on, the decode batch measured
+// 15.67 us against 15.54 (15.41 without this code), and as an out-of-line
+// function, whose callee-saved registers need scratch, 16.1 (the first chunk
+// of a prefill, 4096 short rows: 227 against 83).
+enum : uint32_t {
+    kRareSampled = 1u, kRareIncomplete = 2u, kRareSegmented = 4u, kRareHaveHist = 8u,
+    kRareSplit = 16u, kRareRedo = 32u, kRareClear = 64u, kRareWaits = 128u
+};
+
+template <bool kOrdered>
+__device__ __forceinline__ void finish_rare(const KArgs a, uint32_t C0, uint32_t C1, uint32_t nstored,
+                                            uint32_t xexpect, int team, int team_t,
+                                            uint32_t flags) {
+    Smem &sm = g_sm;
+    const int tid = threadIdx.x;
+    uint32_t item = blockIdx.x;
+    asm volatile("" : "+s"(item));
+    int r, p;
+    int64_t off, L;
+    uint32_t slot;
+    if constexpr (kOrdered) {
+        const uint4 e = a.order[item];
+        asm volatile("" ::"s"(e.x), "s"(e.y), "s"(e.z), "s"(e.w));
+        r = (int)(e.x & 0x3FFFu);
+        p = (int)((e.x >> 14) & 63u);
+        L = (int64_t)(int32_t)e.y;
+        off = (int64_t)((((uint64_t)e.w & 0xFFu) << 32) | e.z);
+        slot = e.w >> 8;
+    } else {
+        p = (int)(item / (uint32_t)a.n_rows);
+        r = (int)(item - (uint32_t)p * (uint32_t)a.n_rows);
+        const int32_t len = a.lens[r];
+        off = a.offs[r];
+        asm volatile("" ::"s"(len), "s"(off));
+        L = (int64_t)len;
+        slot = (uint32_t)r;
+    }
+    const bool sampled = flags & kRareSampled, split = flags & kRareSplit;
+    bool incomplete = flags & kRareIncomplete, segmented = flags & kRareSegmented;
+    bool have_hist = flags & kRareHaveHist, redo = flags & kRareRedo;
+    const bool xclear = flags & kRareClear, waits = flags & kRareWaits;
+    const int64_t nv = view_size(L, view_phase(r, a.s_log2), a.s_log2);
+    char *rb = a.rows + (size_t)slot * kRowBlockBytes;
+    RowState *rs = reinterpret_cast<RowState *>(rb);
+    if (split) {
+        uint32_t *vh = reinterpret_cast<uint32_t *>(rb + kRowStateBytes);
+        uint32_t *xh = reinterpret_cast<uint32_t *>(a.rows + (size_t)a.hdr->split_rows * kRowBlockBytes) +
+                       (size_t)slot * kBins;
+        uint64_t *gc = reinterpret_cast<uint64_t *>(rb + kRowStateBytes + kViewHistBytes);
+        if constexpr (!kOrdered) {
+            if (__builtin_expect(waits || team != 0, 0)) {
+                if (waits) {
+                    // The verdict, waited for as the boundaries are.  Whoever
+                    // leaves without joining a team adds 1 << 32 to the route
+                    // word: after "no team" the last of them clears it; one
+                    // that stopped waiting before the verdict shows in what
+                    // the finisher's own addition returns.
+                    if (tid == 0) {
+                        uint64_t v = 0;
+                        const uint64_t t_wait = wall_clock64();
+                        for (int spin = 0; spin < a.spin_limit; spin++) {
+                            v = __hip_atomic_load(&rs->xtau, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            if ((v & kXGo) || wall_clock64() - t_wait > a.spin_ticks) break;
+                            __builtin_amdgcn_s_sleep(1);
+                        }
+                        if (!(v & kXGo)) atomicAdd(&a.hdr->stats[kStatWaitFallback], 1u);
+                        if ((v & (kXGo | kXAbandon)) != kXGo) {
+                            v = __hip_atomic_fetch_add(&rs->xtau, 1ull << 32, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT);
+                            if ((v & kXAbandon) && (uint32_t)(v >> 32) + 2u == ((uint32_t)(v >> 11) & 0xFFu))
+                                __hip_atomic_store(&rs->xtau, 0ull, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+                        }
+                        sm.xword = v;
+                    }
+                    __syncthreads();
+                    const uint64_t xv = sm.xword;
+                    if ((xv & (kXGo | kXAbandon)) != kXGo) return;
+                    team = (int)((uint32_t)(xv >> 11) & 0xFFu);
+                    team_t = (int)sm.knext;
+                }
+                const int64_t ts = table_seg(L, team);
+                __syncthreads();
+                const TeamResult x = exact_select<true>(
+                    a, sm, r, off, L, (int32_t)(team_t * ts),
+                    (int32_t)min(L, team_t * ts + ts), team, team_t, rs, vh, xh, gc, false);
+                if (!x.alone) {
+                    if (x.done && tid == 0) {
+                        record_team_row(a, sm, r, nv, rs, x);
+                        reset_row_state(rs);
+                    }
+                    return;
+                }
+                redo = true;
+            }
+        }
+        if (__builtin_expect(redo, 0)) {
+            // A segment of the split exact route stopped waiting: this
+            // last arrival runs the row's exact route on its own, which
+            // rewrites every output (the others are done with the row).
+            if constexpr (!kOrdered) {
+                if (tid == 0) {
+                    const uint64_t cc = __hip_atomic_load(&rs->counts, __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT);
+                    sm.wk[2] = (uint32_t)cc;
+                    sm.wk[3] = (uint32_t)(cc >> 32);
+                }
+                __syncthreads();
+            }
+            C1 = sm.wk[2];
+            C0 = sm.wk[3];
+            incomplete = true;
+            nstored = 0;
+            segmented = false;
+            have_hist = false;
+            xexpect = 0;
+            __syncthreads();
+        }
+    }
+    finish_row(a, sm, r, off, L, nv, sampled, C0, C1, incomplete, segmented, nstored, have_hist);
+    PHASE_MARK(a, 5);
+
+    // the row state is reset once every segment is done with it
+    if (split) {
+        if (xexpect) {
+            if (arrive_again(sm, rs, p, kXGo) && tid == 0) reset_row_state(rs);
+        } else if (tid == 0) {
+            reset_row_state(rs, redo || xclear);
+        }
+    }
+}
+
 // kOrdered: the call runs from the item table (a.order set).  Only such calls
 // take the split exact route; the other instance has none of its code (with
 // it, the decode batch measured 3 % slower although it never runs it).
 template <bool kOrdered>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void
 topk_ragged_kernel(KArgs a) {
-    __shared__ Smem sm;
+    Smem &sm = g_sm;
     const int tid = threadIdx.x;
     const int item = blockIdx.x;
 #ifdef TOPK_PHASE_TIMERS
@@ -2432,6 +2799,12 @@ topk_ragged_kernel(KArgs a) {
     // arrivals the finisher expects (0: none)
     bool pushed = false, redo = false;
     uint32_t xexpect = 0;
+    // the row's team for the exact route (0: none), and this member of it
+    int team = 0, team_t = 0;
+    // thread 0: the row's verdict came after every waiting segment had left
+    // (else the last of those that see it clears the route word)
+    bool xclear = false;
+    bool waits = false; // this segment stays for its row's verdict
 
     if (sampled) {
         // A row has at most ceil(L / kSegMin) segments (see below).
@@ -2552,13 +2925,15 @@ topk_ragged_kernel(KArgs a) {
         const uint32_t w8 = (uint32_t)tid >> 6, lane = (uint32_t)lane_id();
         const bool wave_publish = split && P <= kWavePublishMaxSegs && !ordered;
         uint32_t wcnt = 0, dst = 0; // this wave's stored entries, and their first slot
+        uint32_t resv = 0;          // what its (or the workgroup's) reservation returned
+        uint32_t own = 0;           // and the entries that reservation was for
         if (wave_publish) {
             const uint32_t cur_w = sm.wcnt[w8]; // this wave's own count
             if (__builtin_expect(cur_w <= (uint32_t)kWaveCap, 1)) {
                 wcnt = cur_w;
                 uint32_t wres = 0;
                 if (lane == 0 && wcnt)
-                    wres = (uint32_t)__hip_atomic_fetch_add(&rs->sa, (uint64_t)wcnt,
+                    wres = (uint32_t)__hip_atomic_fetch_add(&rs->sa, (uint64_t)wcnt + kReserved,
                                                             __ATOMIC_RELAXED,
                                                             __HIP_MEMORY_SCOPE_AGENT);
                 const uint32_t beg_e = w8 * kWaveStride, end_e = beg_e + wcnt;
@@ -2576,7 +2951,9 @@ topk_ragged_kernel(KArgs a) {
                     __hip_atomic_fetch_max(&rs->amax, mx, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
                 }
-                dst = __builtin_amdgcn_readfirstlane(wres);
+                own = wcnt;
+                resv = __builtin_amdgcn_readfirstlane(wres);
+                dst = resv & (kReserved - 1u);
             } else {
                 const uint2 cc = count_range_wave(a.scores, off, beg, end, sm.cut0, sm.cut1);
                 if (lane == 0) {
@@ -2592,7 +2969,7 @@ topk_ragged_kernel(KArgs a) {
             __syncthreads();
             C1 = sm.cnt;
             incomplete = sm.incomplete != 0;
-            uint32_t wpre = 0, nst = 0, resv = 0;
+            uint32_t wpre = 0, nst = 0;
             if (split) {
                 // (an incomplete segment publishes a histogram instead)
 #pragma unroll
@@ -2602,8 +2979,9 @@ topk_ragged_kernel(KArgs a) {
                     wpre += v < w8 ? cv : 0u;
                     nst += cv;
                 }
+                own = nst;
                 if (tid == 0 && nst)
-                    resv = (uint32_t)__hip_atomic_fetch_add(&rs->sa, (uint64_t)nst,
+                    resv = (uint32_t)__hip_atomic_fetch_add(&rs->sa, (uint64_t)nst + kReserved,
                                                             __ATOMIC_RELAXED,
                                                             __HIP_MEMORY_SCOPE_AGENT);
             }
@@ -2661,7 +3039,7 @@ topk_ragged_kernel(KArgs a) {
             PHASE_MARK(a, 2);
             if (split) {
                 if (tid == 0) {
-                    sm.base = resv;
+                    sm.base = resv & (kReserved - 1u);
                     if (C1 | C0)
                         __hip_atomic_fetch_add(&rs->counts, (uint64_t)C1 | ((uint64_t)C0 << 32),
                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2696,17 +3074,39 @@ topk_ragged_kernel(KArgs a) {
             // writeback or invalidate of the whole L2.  Each wave waits until
             // its own accesses have completed; after the barrier all of them
             // are visible device-wide, before the arrival is made.
+            uint64_t inc = 1ull << 32;
+            if constexpr (!kOrdered) {
+                // Does the row look like one for the exact route?  Then this
+                // segment stays for the finisher's verdict, to be a member of
+                // the row's team.  It goes by the entries reserved when it
+                // reserved its own, scaled to all of the row's reservations
+                // (one a wave, or one a segment), once a quarter of them are
+                // made: a segment's own count says little of its row where
+                // hits come in runs (judged by it, the long split rows waited
+                // in every third segment, and took 1.2 us longer).
+                const uint32_t all = (wave_publish ? kWaves : 1u) * (uint32_t)P;
+                const uint32_t nres = (resv >> 20) + 1u, sum = (resv & (kReserved - 1u)) + own;
+                if (__builtin_expect((4u * nres >= all) &
+                                     ((sum * all > (uint32_t)a.cap * nres) |
+                                      (sum * all * 8u < (uint32_t)a.K * 9u * nres)), 0))
+                    inc |= 1ull << 48;
+            }
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
             if (tid == 0) {
-                const uint64_t old = __hip_atomic_fetch_add(&rs->sa, 1ull << 32, __ATOMIC_RELAXED,
+                const uint64_t old = __hip_atomic_fetch_add(&rs->sa, inc, __ATOMIC_RELAXED,
                                                             __HIP_MEMORY_SCOPE_AGENT);
-                sm.flag = ((uint32_t)(old >> 32) == (uint32_t)(P - 1)) ? 2u : 0u;
-                sm.base = (uint32_t)old; // every segment has reserved by now
+                const uint32_t arrived = (uint32_t)(old >> 32) & 0xFFFFu;
+                sm.flag = (arrived == (uint32_t)(P - 1)) ? 2u : (inc >> 48) ? 1u : 0u;
+                sm.base = (uint32_t)old & (kReserved - 1u); // every segment has reserved by now
+                sm.knext = (uint32_t)(old >> 48); // segments that wait (before this one)
             }
             __syncthreads();
             PHASE_MARK(a, 3);
-            if (sm.flag != 2u) {
+            waits = !kOrdered && sm.flag == 1u;
+            if constexpr (!kOrdered) {
+                if (sm.flag == 0u) return;
+            } else if (sm.flag != 2u) {
                 if (__builtin_expect(!pushed, 1)) return;
                 // Split exact route: wait for the finisher's route word
                 // (bounded as the boundary wait; after it the last arrival
@@ -2743,7 +3143,7 @@ topk_ragged_kernel(KArgs a) {
                 redo = true;
             }
 
-            if (!redo) {
+            if (!redo && !waits) {
             if constexpr (kOrdered) __builtin_amdgcn_s_setprio(2); // (see the boundaries)
             // Finisher (its sm.cut0, cut1, tau0, tau1 are the row's endpoints).
             // The counts and the slot groups that hold candidates are loaded
@@ -2751,6 +3151,7 @@ topk_ragged_kernel(KArgs a) {
             // group hold stale words, ignored), all as agent-scope atomics;
             // each wave loads the counts itself, so no barrier follows.
             const uint32_t stored = sm.base;
+            const uint32_t waiting = kOrdered ? 0u : sm.knext;
             const uint32_t ngroups = (min(stored, (uint32_t)kFront) + kBlock - 1) / kBlock;
             uint32_t c1 = 0, c0 = 0, inc = 0, amx = 0;
             if (lane == 0) {
@@ -2776,6 +3177,33 @@ topk_ragged_kernel(KArgs a) {
             amx = __builtin_amdgcn_readfirstlane(amx);
             incomplete = __builtin_amdgcn_readfirstlane(inc) != 0 || stored > (uint32_t)kFront;
             if (tid == 0) sm.amax = amx; // for the general finish (barriers follow)
+            uint64_t left = 0; // thread 0: the route word before the verdict
+            if constexpr (!kOrdered) {
+                if (__builtin_expect(waiting != 0u, 0)) {
+                    // the verdict: a row for the exact route is run by the
+                    // segments that stayed and this one (in the usual case of
+                    // a row that does not take it, one atomic whose result is
+                    // not waited for until the row is done)
+                    const uint32_t K = (uint32_t)a.K, cap = (uint32_t)a.cap;
+                    const bool exact = C0 > cap || (C0 < K && (C1 < K || C1 > cap));
+                    if (tid == 0)
+                        left = __hip_atomic_fetch_add(
+                            &rs->xtau, kXGo | (exact ? 0ull : kXAbandon) | ((uint64_t)(waiting + 1u) << 11),
+                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (exact) {
+                        team = (int)waiting + 1;
+                        team_t = (int)waiting;
+                        if (tid == 0 && (left >> 32)) {
+                            // members that are gone: no round can complete
+                            __hip_atomic_fetch_or(&rs->team, kAbandoned, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+                            __hip_atomic_fetch_add(&rs->arrive2, (uint32_t)(left >> 32),
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        }
+                    }
+                }
+            }
+            if (!team) {
             nstored = incomplete ? 0u : stored;
             segmented = false;
             PHASE_MARK(a, 4);
@@ -2783,9 +3211,13 @@ topk_ragged_kernel(KArgs a) {
                 finish_fast(a, sm, r, nv, C0, C1, amx, kBlock, (uint32_t)tid, nstored,
                             ngroups, vi, vk)) {
                 PHASE_MARK(a, 5);
-                if (tid == 0) reset_row_state(rs, false); // (no segment took the exact route)
+                if (tid == 0) {
+                    // (no segment took the exact route)
+                    reset_row_state(rs, !kOrdered && waiting && (uint32_t)(left >> 32) == waiting);
+                }
                 return;
             }
+            xclear = !kOrdered && waiting && (uint32_t)(left >> 32) == waiting;
             // general finish: the merged frontier into LDS
             __syncthreads();
 #pragma unroll
@@ -2862,20 +3294,8 @@ topk_ragged_kernel(KArgs a) {
                 }
             }
             __syncthreads();
-            } // !redo
-            if (__builtin_expect(redo, 0)) {
-                // A segment of the split exact route stopped waiting: this
-                // last arrival runs the row's exact route on its own, which
-                // rewrites every output (the others are done with the row).
-                C1 = sm.wk[2];
-                C0 = sm.wk[3];
-                incomplete = true;
-                nstored = 0;
-                segmented = false;
-                have_hist = false;
-                xexpect = 0;
-                __syncthreads();
-            }
+            } // !team
+            } // !redo && !waits
         }
     }
 
@@ -2907,16 +3327,91 @@ topk_ragged_kernel(KArgs a) {
         }
         __syncthreads();
     }
-    finish_row(a, sm, r, off, L, nv, sampled, C0, C1, incomplete, segmented, nstored,
-                      have_hist);
-    PHASE_MARK(a, 5);
+    finish_rare<kOrdered>(
+        a, C0, C1, nstored, xexpect, team, team_t,
+        (sampled ? kRareSampled : 0u) | (incomplete ? kRareIncomplete : 0u) |
+            (segmented ? kRareSegmented : 0u) | (have_hist ? kRareHaveHist : 0u) |
+            (split ? kRareSplit : 0u) | (redo ? kRareRedo : 0u) | (xclear ? kRareClear : 0u) |
+            (waits ? kRareWaits : 0u));
+}
 
-    // the row state is reset once every segment is done with it
-    if (split) {
-        if (xexpect) {
-            if (arrive_again(sm, rs, p, kXGo) && tid == 0) reset_row_state(rs);
-        } else if (tid == 0) {
-            reset_row_state(rs, kOrdered && redo);
+// Calls in which no row is sampled (the policy's floor is above TOPK_L_MAX) and
+// whose rows may be split: a row's segments are the members of its team.  At
+// K = 8192 the decode batch ran its rows on one workgroup each in 60.9 us; in
+// teams of up to eight it takes 27.0.
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void
+topk_exact_kernel(KArgs a) {
+    Smem &sm = g_sm;
+    const int tid = threadIdx.x;
+#ifdef TOPK_PHASE_TIMERS
+    if (a.timers && tid == 0)
+        for (int k = 0; k < 32; k++) g_tmarks[k] = 0;
+    TimerFlush timer_flush{a.timers};
+#endif
+    PHASE_MARK(a, 0);
+    const int p = (int)blockIdx.x / a.n_rows;
+    const int r = (int)blockIdx.x - p * a.n_rows;
+    const int32_t len_r = a.lens[r];
+    const int64_t off = a.offs[r];
+    const int32_t len0 = a.lens[min(tid, a.n_rows - 1)];
+    const uint4 hw = *reinterpret_cast<const uint4 *>(a.hdr); // magic, split_rows, max_rows
+    // (all four in one round trip: see topk_ragged_kernel)
+    asm volatile("" ::"s"(len_r), "s"(off), "s"(hw.x), "s"(hw.y), "s"(hw.z), "v"(len0));
+    const int64_t L = (int64_t)max(len_r, 0);
+    const bool ws_bad = (hw.x != kMagic) | ((uint32_t)a.n_rows > hw.z) |
+                        ((uint32_t)a.n_rows > hw.y);
+    if (ws_bad || L > (int64_t)TOPK_L_MAX) {
+        if (p == 0) {
+            write_error_row(a, r);
+            if (tid == 0 && (!ws_bad || r == 0)) atomicAdd(&a.hdr->stats[kStatErrors], 1u);
+        }
+        return;
+    }
+    if (L <= a.K) {
+        if (p == 0) {
+            write_direct(a, r, a.scores + off, L);
+            if (tid == 0) {
+                atomicAdd(&a.hdr->stats[TOPK_ROUTE_DIRECT], 1u);
+                if (a.trace) {
+                    int32_t *w = a.trace + (int64_t)r * TOPK_TRACE_WORDS;
+                    w[0] = TOPK_ROUTE_DIRECT;
+                    for (int k = 1; k < TOPK_TRACE_WORDS; k++) w[k] = -1;
+                }
+            }
+        }
+        return;
+    }
+    if ((int64_t)p * kSegMin >= L) return; // a row has at most ceil(L / kSegMin) segments
+    int64_t P, seg;
+    segment_plan(a, block_total_length(a, sm.lsum, tid < a.n_rows ? len0 : 0), L, P, seg);
+    if (p >= P) return;
+    PHASE_MARK(a, 16);
+    PHASE_WORD(a, 7, (uint64_t)p | ((uint64_t)P << 16) | ((uint64_t)r << 32));
+    const int32_t beg = (int32_t)(p * seg), end = (int32_t)min(L, p * seg + seg);
+    char *rb = a.rows + (size_t)r * kRowBlockBytes;
+    RowState *rs = reinterpret_cast<RowState *>(rb);
+    uint32_t *vh = reinterpret_cast<uint32_t *>(rb + kRowStateBytes);
+    uint32_t *xh = reinterpret_cast<uint32_t *>(a.rows + (size_t)hw.y * kRowBlockBytes) +
+                   (size_t)r * kBins;
+    uint64_t *gc = reinterpret_cast<uint64_t *>(rb + kRowStateBytes + kViewHistBytes);
+    TeamResult x;
+    x.alone = true;
+    if (P > 1)
+        x = exact_select<true>(a, sm, r, off, L, beg, end, (int)P, p, rs, vh, xh, gc, false);
+    if (x.alone)
+        x = exact_select<false>(a, sm, r, off, L, 0, (int32_t)L, 1, 0, nullptr, nullptr,
+                                nullptr, nullptr, false);
+    if (x.done && tid == 0) {
+        const bool reread = x.eq > (uint32_t)a.cap;
+        atomicAdd(&a.hdr->stats[TOPK_ROUTE_EXACT_UNSAMPLED], 1u);
+        if (reread) atomicAdd(&a.hdr->stats[kStatReread], 1u);
+        if (a.trace) {
+            int32_t *w = a.trace + (int64_t)r * TOPK_TRACE_WORDS;
+            w[0] = TOPK_ROUTE_EXACT_UNSAMPLED | (reread ? TOPK_ROUTE_REREAD_FLAG : 0);
+            w[1] = (int32_t)view_size(L, view_phase(r, a.s_log2), a.s_log2);
+            w[2] = -1; w[3] = -1; w[4] = -1; w[5] = -1;
+            w[6] = (int32_t)x.tstar;
+            w[7] = (int32_t)x.eq;
         }
     }
 }
@@ -3452,7 +3947,12 @@ int launch_call(const float *scores, const int64_t *row_offsets, const int32_t *
         a.order = order;
         grid += extra;
     }
-    if (a.order)
+    if (pmax > 1 && a.l_samp_min > TOPK_L_MAX) {
+        // no row is sampled: teams of up to the resident workgroups
+        a.seg_items = plan_slots(di.cus);
+        hipLaunchKernelGGL(topk_exact_kernel, dim3((unsigned)grid), dim3(kBlock), 0,
+                           (hipStream_t)stream, a);
+    } else if (a.order)
         hipLaunchKernelGGL(topk_ragged_kernel<true>, dim3((unsigned)grid), dim3(kBlock), 0,
                            (hipStream_t)stream, a);
     else
