@@ -255,8 +255,8 @@ int topk_ragged_debug_cutoffs(uint32_t *out_cut, void *stream);
  * key of each row's largest score (0 for an empty row).  workspace: an
  * initialised workspace for at least n_rows rows (as for topk_ragged), whose
  * item-table region receives the work items of a call with more rows than
- * resident workgroups; no other part of it is written.  Same argument errors
- * as topk_ragged. */
+ * resident workgroups (and whose header their bounds); no other part of it is
+ * written.  Same argument errors as topk_ragged. */
 int topk_ragged_debug_read_ceiling(const float *scores, const int64_t *row_offsets,
                                    const int32_t *row_lengths, int32_t n_rows, int32_t K,
                                    uint32_t *out_max, void *workspace, void *stream);

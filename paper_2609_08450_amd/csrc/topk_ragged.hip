@@ -31,6 +31,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <climits>
+#include <cstddef>
 #include <cstdlib>
 #include <mutex>
 #include <type_traits>
@@ -134,20 +135,37 @@ struct RowState {
 };
 static_assert(sizeof(RowState) <= kRowStateBytes, "row state fits its padding");
 
-// Workspace header (first kHeaderBytes of the workspace).
+// Workspace header (first kHeaderBytes of the workspace).  Every workgroup reads
+// its first 32 bytes; the counters have cache lines of their own, and seven
+// of them (4096 short rows 43.4 -> 42.0 us with the counters out of the line
+// that is read; with an atomic of every workgroup on that line at its start,
+// as for claiming work, 300).
+constexpr uint32_t kStatLines = 7;
 struct WsHeader {
     uint32_t magic;
     uint32_t split_rows; // rows with per-row state
     uint32_t max_rows;
     uint32_t cap;
-    uint32_t pad[12];
-    uint32_t stats[16]; // [0..5] routes, [6] reread, [7] wait fallback, [8] errors
+    // a call run from the item table: the first items of its short rows, by the
+    // waves they take (4, 2, 1)
+    uint32_t short_item[3];
+    uint32_t workgroups; // and the workgroups that have work
+    uint32_t pad[24];
+    // [0..5] routes, [6] reread, [7] wait fallback, [8] errors
+    uint32_t stats[kStatLines][32];
 };
+static_assert(sizeof(WsHeader) <= kHeaderBytes, "header size");
+
+enum { kStatReread = 6, kStatWaitFallback = 7, kStatErrors = 8 };
+
+// Adds to a counter, in one of the lines by workgroup.
+__device__ __forceinline__ void count_stat(WsHeader *hdr, uint32_t k, uint32_t v = 1u) {
+    atomicAdd(&hdr->stats[blockIdx.x % kStatLines][k], v);
+}
 
 constexpr uint32_t kReserved = 1u << 20; // one reservation in RowState::sa
 static_assert(kMaxSplit * kFront < (int)kReserved, "a row's reservations fit their field");
 
-enum { kStatReread = 6, kStatWaitFallback = 7, kStatErrors = 8 };
 
 struct KArgs {
     const float *scores;
@@ -1370,7 +1388,7 @@ __device__ __forceinline__ bool team_arrive(const KArgs &a, RowState *rs, uint32
             if (__hip_atomic_compare_exchange_strong(&rs->team, &v, v | kAbandoned,
                                                      __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT)) {
-                atomicAdd(&a.hdr->stats[kStatWaitFallback], 1u);
+                count_stat(a.hdr, kStatWaitFallback);
                 return false;
             }
             continue;
@@ -2070,8 +2088,8 @@ __device__ __forceinline__ void finish_row(const KArgs a, Smem &sm, int r, int64
     }
     PHASE_MARK(a, 13);
     if (threadIdx.x == 0) {
-        atomicAdd(&a.hdr->stats[route & 7u], 1u);
-        if (route & TOPK_ROUTE_REREAD_FLAG) atomicAdd(&a.hdr->stats[kStatReread], 1u);
+        count_stat(a.hdr, route & 7u);
+        if (route & TOPK_ROUTE_REREAD_FLAG) count_stat(a.hdr, kStatReread);
         if (a.trace) {
             int32_t *t = a.trace + (int64_t)r * TOPK_TRACE_WORDS;
             t[0] = (int32_t)route; t[1] = (int32_t)nv;
@@ -2206,7 +2224,7 @@ __device__ __forceinline__ bool finish_fast(const KArgs a, Smem &sm, int r, int6
     }
     PHASE_MARK(a, 13);
     if (tid == 0) {
-        atomicAdd(&a.hdr->stats[route], 1u);
+        count_stat(a.hdr, route);
         if (a.trace) {
             int32_t *t = a.trace + (int64_t)r * TOPK_TRACE_WORDS;
             t[0] = (int32_t)route; t[1] = (int32_t)nv;
@@ -2525,7 +2543,7 @@ __device__ __forceinline__ bool split_exact_final(const KArgs a, Smem &sm, int r
     refine(a, sm, r, false, eq, false, amin, 0u, eq, (uint32_t)a.K - below, (uint32_t)(L - 1));
     PHASE_MARK(a, 13);
     if (tid == 0) {
-        atomicAdd(&a.hdr->stats[TOPK_ROUTE_EXACT_OVERFLOW], 1u);
+        count_stat(a.hdr, TOPK_ROUTE_EXACT_OVERFLOW);
         if (a.trace) {
             int32_t *t = a.trace + (int64_t)r * TOPK_TRACE_WORDS;
             t[0] = TOPK_ROUTE_EXACT_OVERFLOW; t[1] = (int32_t)nv;
@@ -2547,14 +2565,368 @@ __device__ __forceinline__ void record_team_row(const KArgs a, const Smem &sm, i
     const bool under = C0 < (uint32_t)a.K, reread = x.eq > (uint32_t)a.cap;
     const uint32_t route = under && C1 < (uint32_t)a.K ? TOPK_ROUTE_EXACT_UNDERFILL
                                                        : TOPK_ROUTE_EXACT_OVERFLOW;
-    atomicAdd(&a.hdr->stats[route], 1u);
-    if (reread) atomicAdd(&a.hdr->stats[kStatReread], 1u);
+    count_stat(a.hdr, route);
+    if (reread) count_stat(a.hdr, kStatReread);
     if (a.trace) {
         int32_t *w = a.trace + (int64_t)r * TOPK_TRACE_WORDS;
         w[0] = (int32_t)(route | (reread ? TOPK_ROUTE_REREAD_FLAG : 0)); w[1] = (int32_t)nv;
         w[2] = (int32_t)sm.tau0; w[3] = (int32_t)sm.tau1;
         w[4] = (int32_t)C0; w[5] = under ? (int32_t)C1 : -1;
         w[6] = (int32_t)x.tstar; w[7] = (int32_t)x.eq;
+    }
+}
+
+// ------------------------------------------------------ short rows ----
+//
+// Short rows of a call run from the item table: a row takes as many waves as it
+// has 2048 elements (1, 2 or 4), and a workgroup as many rows as its eight
+// waves serve.  Alone in a 512-thread workgroup such a row waits at barriers
+// and for two trips to memory, two rows to a CU at a time (11 us each); here
+// every element sits in a register of its lane from the one read on, and a
+// row's waves wait for each other only.  4096 rows of up to 4096 elements took
+// 78 us and take 40, of which the pre-pass and the dispatch of the workgroups
+// left without work (4.6 ns each past the first 2500) are half.  (One wave a
+// row, streaming it twice: 43 us there, but 35 us for a row of 8000 elements,
+// its steps' latencies in a chain.)
+// The rounds are exact_select's, over a histogram of 16-bit counts (4 KB; a
+// row has fewer than 2^13 elements), with at most 64 kept entries, ranked
+// across the lanes of one wave.
+
+constexpr int kShortRow = 8192;  // rows from this length up take a workgroup each
+constexpr int kShortVecs = 8;    // 16-byte vectors of a lane (2048 elements a wave)
+constexpr uint32_t kShortKeep = 64;
+
+struct alignas(16) ShortLds {
+    uint32_t hist[kBins / 2]; // two bins to a word
+    uint64_t keep[kShortKeep];
+    uint32_t ne, nk;  // outputs and kept entries placed
+    uint32_t sync;    // arrivals of the row's waves
+};
+static_assert(sizeof(ShortLds) * kWaves <= offsetof(Smem, wcnt), "eight rows fit the LDS");
+
+// find_bin over 16-bit counts.
+__device__ __forceinline__ Find short_find(const uint32_t *hist, uint32_t k, bool raw) {
+    const uint32_t lane = (uint32_t)lane_id();
+    const uint32_t grp = raw && lane < 32u ? 31u - lane : lane;
+    const uint4 *h4 = reinterpret_cast<const uint4 *>(hist + 16u * grp);
+    uint32_t c = 0; // (the halves' sums stay below 2^14)
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const uint4 v = h4[j];
+        c += v.x + v.y + v.z + v.w;
+    }
+    c = (c & 0xFFFFu) + (c >> 16);
+    const uint32_t incl = wave_incl_scan(c);
+    Find f;
+    f.bin = kBins; f.below = __builtin_amdgcn_readlane(incl, 63); f.eq = 0;
+    if (k == 0 || k > f.below) return f;
+    const uint32_t owner = (uint32_t)__ffsll((unsigned long long)__ballot(incl >= k)) - 1u;
+    const uint32_t base = __builtin_amdgcn_readlane(incl - c, owner);
+    const uint32_t b = owner * 32u + (lane & 31u), rb = raw ? raw_bin_of(b) : b;
+    const uint32_t v = lane < 32u ? (hist[rb >> 1] >> ((rb & 1u) * 16u)) & 0xFFFFu : 0u;
+    const uint32_t incl2 = wave_incl_scan(v);
+    const int l2 = __ffsll((unsigned long long)__ballot(lane < 32u && base + incl2 >= k)) - 1;
+    f.bin = owner * 32u + (uint32_t)l2;
+    f.below = base + __builtin_amdgcn_readlane(incl2 - v, l2);
+    f.eq = __builtin_amdgcn_readlane(v, l2);
+    return f;
+}
+
+// Barrier of a row's G waves (all of one workgroup, so each arrives); n: the
+// number of barriers so far, this one included.  LDS accesses of a wave
+// complete in order, so its arrival follows its earlier ones.
+__device__ __forceinline__ void row_sync(uint32_t *count, uint32_t G, uint32_t n) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    if (G == 1u) return;
+    if (lane_id() == 0) atomicAdd(count, 1u);
+    while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < G * n)
+        __builtin_amdgcn_s_sleep(1);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The exact route of a row of K < L < kShortRow elements by G waves, this one the
+// t-th (sl: the row's LDS, its counters zero).  Returns tau_star and |Q0|.
+__device__ __forceinline__ uint2 short_row(const KArgs a, ShortLds &sl, int r, int64_t off,
+                                           int32_t L, uint32_t G, uint32_t t) {
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    const uint32_t lane = (uint32_t)lane_id();
+    const uint32_t K = (uint32_t)a.K;
+    const float *row = a.scores + off;
+    // Vector m holds elements i0 + 256 G m ..; past the row a negative NaN,
+    // whose bin follows every value's and whose key is below every window.
+    int32_t i0 = (int32_t)(256u * t + 4u * lane);
+    const int32_t step = (int32_t)(256u * G);
+    const float pad = __builtin_bit_cast(float, 0xFFFFFFFFu);
+    f4 x[kShortVecs];
+#pragma unroll
+    for (int m = 0; m < kShortVecs; m++) {
+        const int32_t i = i0 + m * step;
+        x[m] = f4{pad, pad, pad, pad};
+        if (i + 4 <= L) {
+            const f4u v = *reinterpret_cast<const f4u *>(row + i);
+            x[m] = f4{v.x, v.y, v.z, v.w};
+        } else if (i < L) {
+            x[m].x = row[i];
+            if (i + 1 < L) x[m].y = row[i + 1];
+            if (i + 2 < L) x[m].z = row[i + 2];
+        }
+    }
+    // (keeps what one pass derives from the elements from being kept for the
+    // next: 32 keys and as many masks)
+    auto renew = [&]() {
+#pragma unroll
+        for (int m = 0; m < kShortVecs; m++) asm volatile("" : "+v"(x[m]));
+        asm volatile("" : "+v"(i0));
+    };
+    uint32_t wlo = 0u, whi = ~0u, ilo = 0u, ihi = ~0u, below = 0, eq = 0, tstar = 0, eq0 = 0;
+    bool by_key = true, take_all = false;
+    int shift = 0;
+    uint32_t syncs = 0;
+    for (int round = 0; round < 8; round++) {
+        if (round) row_sync(&sl.sync, G, ++syncs); // the last round's bins have been read
+        uint4 *h4 = reinterpret_cast<uint4 *>(sl.hist);
+        for (uint32_t j = 64u * t + lane; j < kBins / 8; j += 64u * G) h4[j] = make_uint4(0, 0, 0, 0);
+        row_sync(&sl.sync, G, ++syncs);
+        renew();
+        if (round == 0) {
+#pragma unroll
+            for (int m = 0; m < kShortVecs; m++) if (m * step < L) {
+#pragma unroll
+                for (int c = 0; c < 4; c++) {
+                    const uint32_t h = __builtin_bit_cast(uint16_t, (_Float16)x[m][c]);
+                    atomicAdd(&sl.hist[h >> 6], 1u << ((h >> 1) & 16u)); // raw bin h >> 5
+                }
+            }
+        } else {
+            const uint32_t kspan = whi - wlo, ispan = by_key ? ~0u : ihi - ilo;
+#pragma unroll
+            for (int m = 0; m < kShortVecs; m++) if (m * step < L) {
+#pragma unroll
+                for (int c = 0; c < 4; c++) {
+                    const uint32_t u = asc_key(fbits(x[m][c]));
+                    const uint32_t di = (uint32_t)(i0 + m * step + c) - ilo;
+                    if (u - wlo <= kspan && (by_key || di <= ispan)) {
+                        const uint32_t d = (by_key ? whi - u : di) >> shift;
+                        atomicAdd(&sl.hist[d >> 1], 1u << ((d & 1u) * 16u));
+                    }
+                }
+            }
+        }
+        row_sync(&sl.sync, G, ++syncs);
+        const Find f = short_find(sl.hist, K - below, round == 0);
+        take_all = f.eq == K - below - f.below;
+        below += f.below;
+        eq = f.eq;
+        if (round == 0) {
+            tstar = f.bin;
+            eq0 = f.eq;
+            whi = f.bin ? bin_cutoff(f.bin - 1u) - 1u : ~0u;
+            wlo = bin_cutoff(f.bin);
+        } else if (by_key) {
+            const uint64_t b0 = (uint64_t)f.bin << shift, b1 = ((uint64_t)f.bin + 1u) << shift;
+            const uint32_t nlo = b1 > (uint64_t)(whi - wlo) ? wlo : whi - (uint32_t)(b1 - 1u);
+            whi -= (uint32_t)b0;
+            wlo = nlo;
+        } else {
+            ilo += f.bin << shift;
+            ihi = min(ihi, ilo + ((1u << shift) - 1u));
+        }
+        if (take_all || eq <= kShortKeep) break;
+        if (by_key && wlo == whi) {
+            by_key = false;
+            ihi = (uint32_t)(L - 1);
+        }
+        const uint32_t span = by_key ? whi - wlo : ihi - ilo;
+        shift = span ? max(0, 21 - (int)__builtin_clz(span)) : 0;
+    }
+    // Entries above the window go straight to consecutive output slots of the
+    // wave, those of the window to the kept list.
+    const int64_t out0 = (int64_t)r * a.K;
+    auto place = [&](auto simple) {
+        // simple: positive endpoints (raw bits compare as signed integers), no
+        // index window
+        constexpr bool kSimple = decltype(simple)::value;
+        const int32_t t_lo = (int32_t)bits_from_asc(wlo);
+        const int32_t t_hi = take_all ? t_lo : (int32_t)bits_from_asc(whi) + 1;
+        // above the window (or in it, when all of it is taken), and in it or above
+        auto classes = [&](float v, int32_t i, bool &above, bool &hit) {
+            const uint32_t b = fbits(v);
+            if constexpr (kSimple) {
+                above = (int32_t)b >= t_hi;
+                hit = (int32_t)b >= t_lo;
+            } else {
+                const uint32_t u = asc_key(b);
+                hit = u >= wlo && (by_key || u > whi || (uint32_t)i <= ihi);
+                above = hit && (take_all || u > whi || (u == whi && (uint32_t)i < ilo));
+            }
+        };
+        uint32_t ne = 0, nk = 0;
+        if (G > 1u) {
+            // the wave's counts, for its slots among the row's
+#pragma unroll
+            for (int m = 0; m < kShortVecs; m++) if (m * step < L) {
+#pragma unroll
+                for (int c = 0; c < 4; c++) {
+                    bool above, hit;
+                    classes(x[m][c], i0 + m * step + c, above, hit);
+                    ne += (uint32_t)__popcll(__ballot(above));
+                    nk += (uint32_t)__popcll(__ballot(hit));
+                }
+            }
+            nk -= ne;
+            if (lane == 0) {
+                ne = atomicAdd(&sl.ne, ne);
+                nk = atomicAdd(&sl.nk, nk);
+            }
+            ne = __builtin_amdgcn_readfirstlane(ne);
+            nk = __builtin_amdgcn_readfirstlane(nk);
+        }
+        renew();
+#pragma unroll
+        for (int m = 0; m < kShortVecs; m++) if (m * step < L) {
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                bool above, hit;
+                const int32_t i = i0 + m * step + c;
+                const uint32_t b = fbits(x[m][c]);
+                classes(x[m][c], i, above, hit);
+                const uint64_t ma = __ballot(above), mk = __ballot(hit) & ~ma;
+                const uint32_t p = __builtin_amdgcn_mbcnt_hi((uint32_t)(ma >> 32),
+                                       __builtin_amdgcn_mbcnt_lo((uint32_t)ma, ne));
+                if (above) put_out(a, out0, min(p, K - 1u), (uint32_t)i, b); // p < K: always
+                ne += (uint32_t)__popcll(ma);
+                if (mk) {
+                    const uint32_t q = __builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32),
+                                           __builtin_amdgcn_mbcnt_lo((uint32_t)mk, nk));
+                    if (hit && !above && q < kShortKeep) sl.keep[q] = zkey(~asc_key(b), (uint32_t)i);
+                    nk += (uint32_t)__popcll(mk);
+                }
+            }
+        }
+    };
+    renew();
+    if (wlo > 0x80000000u && whi < 0xFFFFFFFFu && by_key) place(std::true_type{});
+    else place(std::false_type{});
+    if (!take_all) {
+        row_sync(&sl.sync, G, ++syncs);
+        if (t == 0u) {
+            const uint32_t nk = min(eq, kShortKeep);
+            const uint64_t z = lane < nk ? sl.keep[lane] : ~0ull;
+            const uint32_t zlo = (uint32_t)z, zhi = (uint32_t)(z >> 32);
+            uint32_t rank = 0;
+            for (uint32_t l = 0; l < nk; l++) {
+                const uint64_t v = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(zhi, l) << 32) |
+                                   (uint32_t)__builtin_amdgcn_readlane(zlo, l);
+                rank += v < z ? 1u : 0u;
+            }
+            if (lane < nk && rank < K - below)
+                put_out(a, out0, below + rank, zlo, bits_from_asc(~zhi));
+        }
+    }
+    return make_uint2(tstar, eq0);
+}
+
+// The outputs of a row of L <= K elements by G waves, 16 bytes at a time (the
+// buffers may be aligned to 4 bytes only).
+__device__ __forceinline__ void short_direct(const KArgs a, int r, int64_t off, int32_t L,
+                                             uint32_t G, uint32_t t) {
+    typedef int32_t i4u __attribute__((ext_vector_type(4), aligned(4)));
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    const float *row = a.scores + off;
+    int32_t *oi = a.out_idx + (int64_t)r * a.K;
+    float *ov = a.out_val + (int64_t)r * a.K;
+    const float ninf = -__builtin_huge_valf();
+    const int32_t K4 = a.K & ~3;
+#pragma unroll 2
+    for (int32_t j = (int32_t)(256u * t) + 4 * lane_id(); j < K4; j += (int32_t)(256u * G)) {
+        i4u i = {-1, -1, -1, -1};
+        f4u v = {ninf, ninf, ninf, ninf};
+        if (j + 4 <= L) {
+            i = i4u{j, j + 1, j + 2, j + 3};
+            v = *reinterpret_cast<const f4u *>(row + j);
+        } else if (j < L) {
+            i.x = j;
+            v.x = row[j];
+            if (j + 1 < L) { i.y = j + 1; v.y = row[j + 1]; }
+            if (j + 2 < L) { i.z = j + 2; v.z = row[j + 2]; }
+        }
+        *reinterpret_cast<i4u *>(oi + j) = i;
+        *reinterpret_cast<f4u *>(ov + j) = v;
+    }
+    const int32_t j = K4 + lane_id();
+    if (t == 0u && j < a.K) {
+        oi[j] = j < L ? j : -1;
+        ov[j] = j < L ? row[j] : ninf;
+    }
+}
+
+// Workgroup b of those for the short items; first: the first item of the rows of
+// 4, 2 and 1 waves each (x, y, z).
+__device__ __forceinline__ void short_group(const KArgs a, Smem &sm, uint32_t b, const uint4 first) {
+    const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t n4 = (first.y - first.x + 1u) / 2u, n2 = (first.z - first.y + 3u) / 4u;
+    uint32_t G, item, last;
+    if (b < n4) {
+        G = 4; item = first.x + 2u * b + (w >> 2); last = first.y;
+    } else if (b < n4 + n2) {
+        G = 2; item = first.y + 4u * (b - n4) + (w >> 1); last = first.z;
+    } else {
+        G = 1; item = first.z + 8u * (b - n4 - n2) + w; last = gridDim.x;
+        if (item - w >= last) return; // past the last item
+    }
+    const uint32_t t = w & (G - 1u);
+    ShortLds &sl = reinterpret_cast<ShortLds *>(&sm)[w - t];
+    const uint4 e = item < last ? a.order[item] : make_uint4(0x80000000u, 0u, 0u, 0u);
+    if (t == 0u && lane_id() == 0) {
+        sl.ne = 0;
+        sl.nk = 0;
+        sl.sync = 0;
+    }
+    const uint32_t ex = __builtin_amdgcn_readfirstlane(e.x);
+    const int32_t L = max((int32_t)__builtin_amdgcn_readfirstlane(e.y), 0);
+    const int64_t off = (int64_t)((((uint64_t)__builtin_amdgcn_readfirstlane(e.w) & 0xFFu) << 32) |
+                                  (uint32_t)__builtin_amdgcn_readfirstlane(e.z));
+    __syncthreads();
+    PHASE_MARK(a, 30);
+    uint32_t counts = 0; // direct | exact << 8 | re-read << 16
+    if (!(ex >> 31)) {
+        const int r = (int)(ex & 0x3FFFu);
+        int32_t route = TOPK_ROUTE_DIRECT;
+        uint2 q = make_uint2(0, 0);
+        if (L <= a.K) {
+            short_direct(a, r, off, L, G, t);
+            counts = 1u;
+        } else {
+            q = short_row(a, sl, r, off, L, G, t);
+            route = TOPK_ROUTE_EXACT_UNSAMPLED;
+            counts = 1u << 8;
+            if (q.y > (uint32_t)a.cap) {
+                route |= TOPK_ROUTE_REREAD_FLAG;
+                counts |= 1u << 16;
+            }
+        }
+        if (a.trace && t == 0u && lane_id() < TOPK_TRACE_WORDS) {
+            const int k = lane_id();
+            int32_t v = k == 0 ? route : -1;
+            if (L > a.K) {
+                if (k == 1) v = (int32_t)view_size(L, view_phase(r, a.s_log2), a.s_log2);
+                if (k == 6) v = (int32_t)q.x;
+                if (k == 7) v = (int32_t)q.y;
+            }
+            a.trace[(int64_t)r * TOPK_TRACE_WORDS + k] = v;
+        }
+    }
+    PHASE_MARK(a, 31);
+    // one addition a workgroup and counter (thousands of waves adding to one
+    // address would outlast the rows themselves)
+    if (lane_id() == 0) sm.wc[w] = t == 0u ? counts : 0u;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t c = 0;
+        for (int v = 0; v < kWaves; v++) c += sm.wc[v];
+        if (c & 0xFFu) count_stat(a.hdr, TOPK_ROUTE_DIRECT, c & 0xFFu);
+        if ((c >> 8) & 0xFFu) count_stat(a.hdr, TOPK_ROUTE_EXACT_UNSAMPLED, (c >> 8) & 0xFFu);
+        if (c >> 16) count_stat(a.hdr, kStatReread, c >> 16);
     }
 }
 
@@ -2628,7 +3000,7 @@ __device__ __forceinline__ void finish_rare(const KArgs a, uint32_t C0, uint32_t
                             if ((v & kXGo) || wall_clock64() - t_wait > a.spin_ticks) break;
                             __builtin_amdgcn_s_sleep(1);
                         }
-                        if (!(v & kXGo)) atomicAdd(&a.hdr->stats[kStatWaitFallback], 1u);
+                        if (!(v & kXGo)) count_stat(a.hdr, kStatWaitFallback);
                         if ((v & (kXGo | kXAbandon)) != kXGo) {
                             v = __hip_atomic_fetch_add(&rs->xtau, 1ull << 32, __ATOMIC_RELAXED,
                                                        __HIP_MEMORY_SCOPE_AGENT);
@@ -2722,11 +3094,24 @@ topk_ragged_kernel(KArgs a) {
     // (an item-table call never splits by plan and takes the row from its
     // entry: it loads no length or offset, and its wait holds no vector load,
     // which under load would queue behind the other workgroup's stream)
+    const uint4 hw = *reinterpret_cast<const uint4 *>(a.hdr); // magic, split_rows, max_rows
+    if constexpr (kOrdered) {
+        // Workgroups without work leave after one trip to a line that all of
+        // them read.  From the first short row's item on, several rows to a
+        // workgroup (with a bad workspace, below, one).
+        const uint4 hs = reinterpret_cast<const uint4 *>(a.hdr)[1]; // short_item, workgroups
+        if (hw.x == kMagic && (uint32_t)a.n_rows <= hw.z) {
+            if ((uint32_t)item >= hs.w) return;
+            if ((uint32_t)item >= hs.x) {
+                short_group(a, sm, (uint32_t)item - hs.x, hs);
+                return;
+            }
+        }
+    }
     const uint4 e = *(ordered ? a.order + item : reinterpret_cast<const uint4 *>(a.hdr));
     const int32_t len_i = ordered ? 0 : a.lens[ri];
     const int64_t off_i = ordered ? 0 : a.offs[ri];
     const int32_t len0_raw = ordered ? 0 : a.lens[min(tid, a.n_rows - 1)];
-    const uint4 hw = *reinterpret_cast<const uint4 *>(a.hdr); // magic, split_rows, max_rows
     // (keeps the compiler from sinking each load to its first use, which
     // would make them several round trips instead of one)
     asm volatile("" ::"s"(e.x), "s"(e.y), "s"(e.z), "s"(e.w), "s"(len_i), "s"(off_i), "s"(hw.x),
@@ -2752,7 +3137,7 @@ topk_ragged_kernel(KArgs a) {
     if (__builtin_expect(ws_bad, 0)) {
         if (p == 0) {
             write_error_row(a, r);
-            if (tid == 0 && r == 0) atomicAdd(&a.hdr->stats[kStatErrors], 1u);
+            if (tid == 0 && r == 0) count_stat(a.hdr, kStatErrors);
         }
         return;
     }
@@ -2761,7 +3146,7 @@ topk_ragged_kernel(KArgs a) {
     if (__builtin_expect(L > (int64_t)TOPK_L_MAX, 0)) {
         if (p == 0) {
             write_error_row(a, r);
-            if (tid == 0) atomicAdd(&a.hdr->stats[kStatErrors], 1u);
+            if (tid == 0) count_stat(a.hdr, kStatErrors);
         }
         return;
     }
@@ -2770,7 +3155,7 @@ topk_ragged_kernel(KArgs a) {
         if (p == 0) {
             write_direct(a, r, row, L);
             if (tid == 0) {
-                atomicAdd(&a.hdr->stats[TOPK_ROUTE_DIRECT], 1u);
+                count_stat(a.hdr, TOPK_ROUTE_DIRECT);
                 if (a.trace) {
                     int32_t *t = a.trace + (int64_t)r * TOPK_TRACE_WORDS;
                     t[0] = TOPK_ROUTE_DIRECT;
@@ -2893,7 +3278,7 @@ topk_ragged_kernel(KArgs a) {
                         sm.cut1 = bin_cutoff(sm.tau1);
                     } else {
                         sm.flag = 0u;
-                        atomicAdd(&a.hdr->stats[kStatWaitFallback], 1u);
+                        count_stat(a.hdr, kStatWaitFallback);
                     }
                 }
                 __syncthreads();
@@ -3120,7 +3505,7 @@ topk_ragged_kernel(KArgs a) {
                         __builtin_amdgcn_s_sleep(1);
                     }
                     sm.xword = v;
-                    if (!(v & kXGo)) atomicAdd(&a.hdr->stats[kStatWaitFallback], 1u);
+                    if (!(v & kXGo)) count_stat(a.hdr, kStatWaitFallback);
                 }
                 __syncthreads();
                 PHASE_MARK(a, 29);
@@ -3363,7 +3748,7 @@ topk_exact_kernel(KArgs a) {
     if (ws_bad || L > (int64_t)TOPK_L_MAX) {
         if (p == 0) {
             write_error_row(a, r);
-            if (tid == 0 && (!ws_bad || r == 0)) atomicAdd(&a.hdr->stats[kStatErrors], 1u);
+            if (tid == 0 && (!ws_bad || r == 0)) count_stat(a.hdr, kStatErrors);
         }
         return;
     }
@@ -3371,7 +3756,7 @@ topk_exact_kernel(KArgs a) {
         if (p == 0) {
             write_direct(a, r, a.scores + off, L);
             if (tid == 0) {
-                atomicAdd(&a.hdr->stats[TOPK_ROUTE_DIRECT], 1u);
+                count_stat(a.hdr, TOPK_ROUTE_DIRECT);
                 if (a.trace) {
                     int32_t *w = a.trace + (int64_t)r * TOPK_TRACE_WORDS;
                     w[0] = TOPK_ROUTE_DIRECT;
@@ -3403,8 +3788,8 @@ topk_exact_kernel(KArgs a) {
                                 nullptr, nullptr, false);
     if (x.done && tid == 0) {
         const bool reread = x.eq > (uint32_t)a.cap;
-        atomicAdd(&a.hdr->stats[TOPK_ROUTE_EXACT_UNSAMPLED], 1u);
-        if (reread) atomicAdd(&a.hdr->stats[kStatReread], 1u);
+        count_stat(a.hdr, TOPK_ROUTE_EXACT_UNSAMPLED);
+        if (reread) count_stat(a.hdr, kStatReread);
         if (a.trace) {
             int32_t *w = a.trace + (int64_t)r * TOPK_TRACE_WORDS;
             w[0] = TOPK_ROUTE_EXACT_UNSAMPLED | (reread ? TOPK_ROUTE_REREAD_FLAG : 0);
@@ -3431,11 +3816,12 @@ __device__ __forceinline__ uint32_t length_class(int32_t L) {
 // One workgroup; n <= kOrderMaxRows, extra <= kOrderExtra.  Thread t takes
 // rows [R t, R (t + 1)), and a run of equal classes among them takes one LDS
 // atomic: rows of similar length would otherwise all add into one counter at
-// once.  R = 1 when the rows fit the workgroup (each row's rank costs its
-// thread a dependent LDS atomic: a call of 1024 rows of random lengths spent
-// 3.5 us ranking on one wave), else kOrderPer, which places each wave's 1024
-// rows of a class as one block (smaller blocks made the chunked-prefill block
-// 2 % slower: see the order's measurements).
+// once.  R is the smallest of 1, 4 and kOrderPer whose threads hold every row
+// (each row's rank costs its thread a dependent LDS atomic: a call of 1024
+// rows of random lengths spent 3.5 us ranking on one wave; 4096 rows on four
+// waves, with R = kOrderPer, made the chunked-prefill block 435 us instead of
+// 430, 2000 rows of 65K elements 141 instead of 130, and the first chunk of a
+// prefill 42 instead of 40).
 //
 // Splitting (KV-split mapping, Section 4.5, for calls too large to split
 // every row): a sampled row among the kOrderBlock longest gets
@@ -3449,7 +3835,7 @@ __device__ __forceinline__ uint32_t length_class(int32_t L) {
 template <int R>
 __global__ __launch_bounds__(kOrderBlock) void row_order_kernel(KArgs a, uint4 *order,
                                                                 int32_t extra, int32_t slots) {
-    static_assert(R == 1 || R == kOrderPer, "rows per thread");
+    static_assert(R == 1 || R == 4 || R == kOrderPer, "rows per thread");
     constexpr uint32_t kNone = 256; // class of a position past the last row
     constexpr int kW = kOrderBlock / 64;
     __shared__ uint32_t cnt[256];
@@ -3459,53 +3845,59 @@ __global__ __launch_bounds__(kOrderBlock) void row_order_kernel(KArgs a, uint4 *
     __shared__ uint32_t wtot[kW];
     __shared__ int64_t lsum[kW];
     __shared__ uint32_t ecap_s;
+    __shared__ uint32_t short_s[3]; // ranks of the first short rows of 4, 2 and 1 waves
     const int n = a.n_rows;
     const int tid = threadIdx.x;
     const int w = tid >> 6;
     const int i0 = tid * R;
     if (tid < 256) cnt[tid] = 0;
+    // short rows: of the classes below that of kShortRow elements or the
+    // sampling floor, and below a half and a quarter of kShortRow those of
+    // fewer waves
+    auto short_cls = [&](int k) { return length_class(min(kShortRow >> k, a.l_samp_min)); };
     if (tid == 0) ecap_s = 0;
+    if (tid < 3) short_s[tid] = (uint32_t)n;
     rlen[tid] = 0;
     const uint32_t max_split = a.hdr->split_rows;
-    int32_t Ls[kOrderPer];
-    int64_t Os[kOrderPer]; // loaded with the lengths: one round trip to memory
+    int32_t Ls[R];
+    int64_t Os[R]; // loaded with the lengths: one round trip to memory
     // (16-byte loads where the arrays allow and a thread takes kOrderPer
     // rows: its rows are contiguous, so the lanes of one load are 64 bytes
     // apart)
-    const bool vec = R == kOrderPer && ((reinterpret_cast<uintptr_t>(a.lens) |
-                       reinterpret_cast<uintptr_t>(a.offs)) & 15u) == 0 && i0 + kOrderPer <= n;
+    const bool vec = R >= 4 && ((reinterpret_cast<uintptr_t>(a.lens) |
+                       reinterpret_cast<uintptr_t>(a.offs)) & 15u) == 0 && i0 + R <= n;
     if (vec) {
         const int4 *l4 = reinterpret_cast<const int4 *>(a.lens + i0);
         const longlong2 *o2 = reinterpret_cast<const longlong2 *>(a.offs + i0);
 #pragma unroll
-        for (int q = 0; q < kOrderPer / 4; q++) {
+        for (int q = 0; q < R / 4; q++) {
             const int4 v = l4[q];
             Ls[4 * q] = v.x; Ls[4 * q + 1] = v.y; Ls[4 * q + 2] = v.z; Ls[4 * q + 3] = v.w;
         }
 #pragma unroll
-        for (int q = 0; q < kOrderPer / 2; q++) {
+        for (int q = 0; q < R / 2; q++) {
             const longlong2 v = o2[q];
             Os[2 * q] = v.x; Os[2 * q + 1] = v.y;
         }
     } else {
 #pragma unroll
-        for (int j = 0; j < kOrderPer; j++) {
-            Ls[j] = j < R && i0 + j < n ? a.lens[i0 + j] : 0;
-            Os[j] = j < R && i0 + j < n ? a.offs[i0 + j] : 0;
+        for (int j = 0; j < R; j++) {
+            Ls[j] = i0 + j < n ? a.lens[i0 + j] : 0;
+            Os[j] = i0 + j < n ? a.offs[i0 + j] : 0;
         }
     }
-    uint32_t cls[kOrderPer], run[kOrderPer]; // run[j]: rows of j's run from j on
+    uint32_t cls[R], run[R]; // run[j]: rows of j's run from j on
 #pragma unroll
-    for (int j = 0; j < kOrderPer; j++)
-        cls[j] = j < R && i0 + j < n ? length_class(Ls[j]) : kNone;
-    run[kOrderPer - 1] = 1;
+    for (int j = 0; j < R; j++)
+        cls[j] = i0 + j < n ? length_class(Ls[j]) : kNone;
+    run[R - 1] = 1;
 #pragma unroll
-    for (int j = kOrderPer - 2; j >= 0; j--) run[j] = cls[j] == cls[j + 1] ? run[j + 1] + 1 : 1;
+    for (int j = R - 2; j >= 0; j--) run[j] = cls[j] == cls[j + 1] ? run[j + 1] + 1 : 1;
     // the call's total length (at most 2^14 rows of < 2^31: wave sums of the
     // bits [0,16), [16,32) and [32,36) of each thread's sum fit 32 bits)
     uint64_t ls = 0;
 #pragma unroll
-    for (int j = 0; j < kOrderPer; j++) ls += cls[j] != kNone ? (uint64_t)max(Ls[j], 0) : 0u;
+    for (int j = 0; j < R; j++) ls += cls[j] != kNone ? (uint64_t)max(Ls[j], 0) : 0u;
     {
         const uint32_t lo = wave_incl_scan((uint32_t)ls & 0xFFFFu);
         const uint32_t mid = wave_incl_scan((uint32_t)(ls >> 16) & 0xFFFFu);
@@ -3514,7 +3906,7 @@ __global__ __launch_bounds__(kOrderBlock) void row_order_kernel(KArgs a, uint4 *
     }
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kOrderPer; j++)
+    for (int j = 0; j < R; j++)
         if (cls[j] != kNone && (j == 0 || cls[j] != cls[j - 1])) atomicAdd(&cnt[cls[j]], run[j]);
     __syncthreads();
     if (tid < 64) {
@@ -3525,7 +3917,13 @@ __global__ __launch_bounds__(kOrderBlock) void row_order_kernel(KArgs a, uint4 *
         for (int k = 0; k < 4; k++) { c4[k] = cnt[255 - 4 * tid - k]; t += c4[k]; }
         uint32_t acc = wave_incl_scan(t) - t;
 #pragma unroll
-        for (int k = 0; k < 4; k++) { cnt[255 - 4 * tid - k] = acc; acc += c4[k]; }
+        for (int k = 0; k < 4; k++) {
+            cnt[255 - 4 * tid - k] = acc;
+#pragma unroll
+            for (int q = 0; q < 3; q++)
+                if (256u - 4u * (uint32_t)tid - (uint32_t)k == short_cls(q)) short_s[q] = acc;
+            acc += c4[k];
+        }
     }
     int64_t total = 0;
 #pragma unroll
@@ -3535,10 +3933,10 @@ __global__ __launch_bounds__(kOrderBlock) void row_order_kernel(KArgs a, uint4 *
     const float rS = __builtin_amdgcn_rcpf((float)S);
     __syncthreads();
     // ranks; the desired segments of the kOrderBlock longest rows
-    uint32_t rk[kOrderPer];
+    uint32_t rk[R];
     uint32_t pos = 0;
 #pragma unroll
-    for (int j = 0; j < kOrderPer; j++) {
+    for (int j = 0; j < R; j++) {
         rk[j] = 0xFFFFFFFFu;
         if (cls[j] == kNone) continue;
         if (j == 0 || cls[j] != cls[j - 1]) pos = atomicAdd(&cnt[cls[j]], run[j]);
@@ -3588,8 +3986,22 @@ __global__ __launch_bounds__(kOrderBlock) void row_order_kernel(KArgs a, uint4 *
     }
     __syncthreads();
     const uint32_t ecap = ecap_s;
+    if (tid == 0) {
+        // Short rows share workgroups in calls whose other items are all
+        // resident at once.  In others they are the last to start, and a
+        // workgroup of several lasts longer than one of a single row (15-19
+        // against 11 us while the long rows stream): the edge mix took 74.5 us
+        // with them together, 71.2 each alone.
+        uint32_t s0 = short_s[0], s1 = short_s[1], s2 = short_s[2];
+        if (s0 + ecap > (uint32_t)slots) s0 = s1 = s2 = (uint32_t)n;
+        a.hdr->short_item[0] = s0 + ecap; // (cut rows are longer)
+        a.hdr->short_item[1] = s1 + ecap;
+        a.hdr->short_item[2] = s2 + ecap;
+        a.hdr->workgroups = s0 + ecap + (s1 - s0 + 1u) / 2u + (s2 - s1 + 3u) / 4u +
+                            ((uint32_t)n - s2 + 7u) / 8u;
+    }
 #pragma unroll
-    for (int j = 0; j < kOrderPer; j++) {
+    for (int j = 0; j < R; j++) {
         if (rk[j] == 0xFFFFFFFFu) continue;
         const uint32_t k = rk[j];
         uint32_t base = k + ecap, P = 1, slot = 0;
@@ -3622,13 +4034,13 @@ __global__ void ws_init_kernel(WsHeader *hdr, char *rows, uint32_t split_rows, u
         hdr->split_rows = split_rows;
         hdr->max_rows = max_rows;
         hdr->cap = cap;
-        for (int s = 0; s < 16; s++) hdr->stats[s] = 0;
+        for (uint32_t s = 0; s < kStatLines * 32u; s++) hdr->stats[s / 32u][s % 32u] = 0;
         hdr->magic = kMagic;
     }
 }
 
 __global__ void stats_reset_kernel(WsHeader *hdr) {
-    if (threadIdx.x < 16) hdr->stats[threadIdx.x] = 0;
+    if (threadIdx.x < kStatLines * 32u) hdr->stats[threadIdx.x / 32u][threadIdx.x % 32u] = 0;
 }
 
 __global__ void debug_coarse_kernel(const float *x, int64_t n, uint16_t *out) {
@@ -3940,6 +4352,9 @@ int launch_call(const float *scores, const int64_t *row_offsets, const int32_t *
         if (n_rows <= kOrderBlock)
             hipLaunchKernelGGL(row_order_kernel<1>, dim3(1), dim3(kOrderBlock), 0,
                                (hipStream_t)stream, a, order, extra, plan_slots(di.cus));
+        else if (n_rows <= 4 * kOrderBlock)
+            hipLaunchKernelGGL(row_order_kernel<4>, dim3(1), dim3(kOrderBlock), 0,
+                               (hipStream_t)stream, a, order, extra, plan_slots(di.cus));
         else
             hipLaunchKernelGGL(row_order_kernel<kOrderPer>, dim3(1), dim3(kOrderBlock), 0,
                                (hipStream_t)stream, a, order, extra, plan_slots(di.cus));
@@ -4049,16 +4464,19 @@ int topk_ragged_read_stats(void *workspace, topk_ragged_stats *out, void *stream
     if (!workspace || !out) return TOPK_EINVAL;
     if (reinterpret_cast<uintptr_t>(workspace) % kWorkspaceAlign) return TOPK_EINVAL;
     WsHeader *hdr = static_cast<WsHeader *>(workspace);
-    uint32_t st[16];
+    uint32_t lines[kStatLines][32];
     hipStream_t s = (hipStream_t)stream;
-    if (hipMemcpyAsync(st, hdr->stats, sizeof st, hipMemcpyDeviceToHost, s) != hipSuccess)
+    if (hipMemcpyAsync(lines, hdr->stats, sizeof lines, hipMemcpyDeviceToHost, s) != hipSuccess)
         return TOPK_ELAUNCH;
     if (hipStreamSynchronize(s) != hipSuccess) return TOPK_ELAUNCH;
+    uint64_t st[9] = {};
+    for (uint32_t q = 0; q < kStatLines; q++)
+        for (int k = 0; k < 9; k++) st[k] += lines[q][k];
     for (int i = 0; i < 6; i++) out->route[i] = st[i];
     out->reread = st[kStatReread];
     out->wait_fallback = st[kStatWaitFallback];
     out->errors = st[kStatErrors];
-    hipLaunchKernelGGL(stats_reset_kernel, dim3(1), dim3(64), 0, s, hdr);
+    hipLaunchKernelGGL(stats_reset_kernel, dim3(1), dim3(kStatLines * 32), 0, s, hdr);
     return hipGetLastError() == hipSuccess ? TOPK_OK : TOPK_ELAUNCH;
 }
 
@@ -4115,6 +4533,9 @@ int topk_ragged_debug_read_ceiling(const float *scores, const int64_t *row_offse
         uint4 *order = reinterpret_cast<uint4 *>(static_cast<char *>(workspace) + kHeaderBytes);
         if (n_rows <= kOrderBlock)
             hipLaunchKernelGGL(row_order_kernel<1>, dim3(1), dim3(kOrderBlock), 0,
+                               (hipStream_t)stream, a, order, extra, plan_slots(di.cus));
+        else if (n_rows <= 4 * kOrderBlock)
+            hipLaunchKernelGGL(row_order_kernel<4>, dim3(1), dim3(kOrderBlock), 0,
                                (hipStream_t)stream, a, order, extra, plan_slots(di.cus));
         else
             hipLaunchKernelGGL(row_order_kernel<kOrderPer>, dim3(1), dim3(kOrderBlock), 0,
