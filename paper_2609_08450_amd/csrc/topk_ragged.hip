@@ -2636,6 +2636,10 @@ __device__ __forceinline__ Find short_find(const uint32_t *hist, uint32_t k, boo
 // number of barriers so far, this one included.  LDS accesses of a wave
 // complete in order, so its arrival follows its earlier ones.
 __device__ __forceinline__ void row_sync(uint32_t *count, uint32_t G, uint32_t n) {
+    if (G == (uint32_t)kWaves) {
+        __syncthreads();
+        return;
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     if (G == 1u) return;
     if (lane_id() == 0) atomicAdd(count, 1u);
@@ -2973,6 +2977,32 @@ __device__ __forceinline__ void finish_rare(const KArgs a, uint32_t C0, uint32_t
         slot = (uint32_t)r;
     }
     const bool sampled = flags & kRareSampled, split = flags & kRareSplit;
+    if (!kOrdered && !sampled && L < (int64_t)kShortRow) {
+        // a short row alone, on all eight waves (the tiny batch 9.8 -> 8.3 us; in
+        // a call run from the item table, among streaming rows, no gain)
+        ShortLds &sl = reinterpret_cast<ShortLds &>(sm);
+        if (tid == 0) {
+            sl.ne = 0;
+            sl.nk = 0;
+        }
+        __syncthreads();
+        const uint2 q = short_row(a, sl, r, off, (int32_t)L, (uint32_t)kWaves,
+                                  (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6));
+        if (tid == 0) {
+            const bool reread = q.y > (uint32_t)a.cap;
+            count_stat(a.hdr, TOPK_ROUTE_EXACT_UNSAMPLED);
+            if (reread) count_stat(a.hdr, kStatReread);
+            if (a.trace) {
+                int32_t *w = a.trace + (int64_t)r * TOPK_TRACE_WORDS;
+                w[0] = TOPK_ROUTE_EXACT_UNSAMPLED | (reread ? TOPK_ROUTE_REREAD_FLAG : 0);
+                w[1] = (int32_t)view_size(L, view_phase(r, a.s_log2), a.s_log2);
+                w[2] = -1; w[3] = -1; w[4] = -1; w[5] = -1;
+                w[6] = (int32_t)q.x;
+                w[7] = (int32_t)q.y;
+            }
+        }
+        return;
+    }
     bool incomplete = flags & kRareIncomplete, segmented = flags & kRareSegmented;
     bool have_hist = flags & kRareHaveHist, redo = flags & kRareRedo;
     const bool xclear = flags & kRareClear, waits = flags & kRareWaits;
