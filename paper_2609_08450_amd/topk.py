@@ -123,17 +123,27 @@ def _ptr(t: torch.Tensor | None, dtype=None, name=""):
         return None
     if not t.is_cuda:
         raise TopkError(f"{name} must be a device tensor")
-    if dtype is not None and t.dtype != dtype:
+    if dtype is not None and t.dtype is not dtype:
         raise TopkError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise TopkError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+# The current device's current stream as a handle.  torch.cuda.current_stream()
+# makes a Stream object on each call; a small call's host time (9.5 us, 5.6 of
+# it in this module) is longer than its kernel's, so the call path below makes
+# no objects: addresses and handles are passed as integers.
+_current_device = torch._C._cuda_getDevice if hasattr(torch._C, "_cuda_getDevice") else None
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream):
     if stream is None:
+        if _current_raw_stream is not None and _current_device is not None:
+            return _current_raw_stream(_current_device())
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def default_policy() -> Policy:
@@ -173,7 +183,7 @@ def alloc_workspace(max_rows: int, K: int, device="cuda", stream=None) -> torch.
 def topk_ragged(scores, row_offsets, row_lengths, n_rows: int, K: int, out_idx, out_val,
                 workspace, stream=None) -> None:
     """Forwards to topk_ragged(); see include/topk_ragged.h for the contract."""
-    _check(lib().topk_ragged(_ptr(scores, torch.float32, "scores"),
+    _check((_lib or lib()).topk_ragged(_ptr(scores, torch.float32, "scores"),
                              _ptr(row_offsets, torch.int64, "row_offsets"),
                              _ptr(row_lengths, torch.int32, "row_lengths"), n_rows, K,
                              _ptr(out_idx, torch.int32, "out_idx"),
@@ -256,7 +266,7 @@ class TopK:
 
     def __call__(self, scores, row_offsets, row_lengths, out_idx=None, out_val=None,
                  policy: Policy | None = None, row_trace=None, stream=None):
-        n = int(row_lengths.numel())
+        n = row_lengths.numel()
         if n > self.max_rows:
             raise TopkError(f"{n} rows exceed the workspace's {self.max_rows}")
         if out_idx is None:
