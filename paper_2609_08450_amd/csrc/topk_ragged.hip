@@ -132,6 +132,7 @@ struct RowState {
     // waits for the others, and selects in its own range):
     uint64_t team;       // arrivals at the rounds' barriers | abandoned << 32
     uint64_t tslots;     // outputs reserved | kept entries reserved << 32
+    uint32_t tbound;     // 2047 - the last coarse bin that every member has added
 };
 static_assert(sizeof(RowState) <= kRowStateBytes, "row state fits its padding");
 
@@ -1407,6 +1408,7 @@ __device__ __forceinline__ void team_reset(RowState *rs, uint32_t *vh, uint32_t 
         __hip_atomic_store(&rs->team, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&rs->tslots, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&rs->arrive2, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&rs->tbound, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -1466,13 +1468,16 @@ __device__ __forceinline__ TeamResult exact_select(const KArgs a, Smem &sm, int 
     TeamResult res;
     res.tstar = 0; res.eq = 0; res.done = false; res.alone = false;
     bool passed = true;
+    // coarse: the round is over coarse bins; full: over all of them (a team's
+    // first round leaves the far bins out, below)
+    bool coarse = true, full = !kTeam;
     int round = 0;
     for (;; round++) {
-        if (round || !have_hist) {
-            if (round) __syncthreads(); // the last round's bins have been read
+        if (round) __syncthreads(); // the last round's bins have been read
+        if (coarse ? round == 0 && !have_hist : true) {
             clear_hist(sm);
             __syncthreads();
-            if (round == 0) {
+            if (coarse) {
                 pass([&](const f4 *x, const int32_t *i0, int32_t lo, int32_t hi, bool edge,
                          int32_t mv) {
 #pragma unroll
@@ -1506,7 +1511,7 @@ __device__ __forceinline__ TeamResult exact_select(const KArgs a, Smem &sm, int 
                 });
             }
         }
-        const bool raw = round == 0 && !have_hist;
+        const bool raw = coarse && !have_hist;
         __syncthreads();
         PHASE_MARK(a, 21);
         const uint4 h = reinterpret_cast<const uint4 *>(sm.hist)[tid];
@@ -1514,7 +1519,32 @@ __device__ __forceinline__ TeamResult exact_select(const KArgs a, Smem &sm, int 
         const uint32_t *H = sm.hist, *G = sm.coarse[0];
         if constexpr (kTeam) {
             uint32_t *d = gb[round % 3] + 4 * tid;
-            add_bins(d, h);
+            uint4 ha = h;
+            if (coarse && !full) {
+                // Only the bins that can hold the row's K-th entry, as far as
+                // this member can tell: twice its share of the K entries and
+                // 64 more.  (A team's additions into one histogram queue: of
+                // all bins they took 2.7 us at K = 8192, 5 in the slower
+                // rows.)  When tau_star is not among the bins that all members
+                // added, a second round adds all of them.
+                __syncthreads(); // the group sums
+                const uint32_t n = (uint32_t)(end - beg);
+                const uint64_t share = 2ull * K * n / (uint64_t)L + 64u;
+                const uint32_t bound = share < n
+                    ? find_bin(sm.hist, sm.coarse[0], (uint32_t)share, true).bin : (uint32_t)kBins - 1u;
+                auto near = [&](uint32_t k) {
+                    const uint32_t b = 4u * (uint32_t)tid + k;
+                    return raw_bin_of(b) <= bound; // (its own inverse)
+                };
+                ha.x = near(0) ? h.x : 0u;
+                ha.y = near(1) ? h.y : 0u;
+                ha.z = near(2) ? h.z : 0u;
+                ha.w = near(3) ? h.w : 0u;
+                if (tid == 0)
+                    __hip_atomic_fetch_max(&rs->tbound, (uint32_t)kBins - 1u - bound,
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            add_bins(d, ha);
             // member 0 clears the histogram of the round after next (the
             // others' first additions to it follow the next barrier); vh and
             // xh are clear for the first two rounds
@@ -1532,6 +1562,8 @@ __device__ __forceinline__ TeamResult exact_select(const KArgs a, Smem &sm, int 
             const uint64_t m1 = __hip_atomic_load(m + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const uint4 hm = make_uint4((uint32_t)m0, (uint32_t)(m0 >> 32), (uint32_t)m1,
                                         (uint32_t)(m1 >> 32));
+            if (coarse && !full && tid == 0)
+                sm.base = __hip_atomic_load(&rs->tbound, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             reinterpret_cast<uint4 *>(sm.hist2)[tid] = hm;
             group_sums_of(hm, sm.coarse[1]);
             H = sm.hist2;
@@ -1541,6 +1573,10 @@ __device__ __forceinline__ TeamResult exact_select(const KArgs a, Smem &sm, int 
         const uint32_t need0 = K - below;
         const Find f = find_bin(H, G, need0, raw);
         if constexpr (kTeam) {
+            if (coarse && !full && f.bin > (uint32_t)kBins - 1u - sm.base) {
+                full = true;
+                continue;
+            }
             const uint2 own = bin_counts(sm.hist, sm.coarse[0], f.bin, raw);
             own_lt += own.x;
             own_eq = own.y;
@@ -1549,7 +1585,8 @@ __device__ __forceinline__ TeamResult exact_select(const KArgs a, Smem &sm, int 
         below += f.below;
         eq = f.eq;
         take_all = f.eq == need0 - f.below;
-        if (round == 0) {
+        if (coarse) {
+            coarse = false;
             res.tstar = f.bin;
             res.eq = f.eq;
             whi = f.bin ? bin_cutoff(f.bin - 1u) - 1u : ~0u;
@@ -1566,7 +1603,7 @@ __device__ __forceinline__ TeamResult exact_select(const KArgs a, Smem &sm, int 
         }
         // (every round leaves less than 2^-10 of its window, so three rounds
         // of the key and three of the index end the search)
-        if (take_all || eq <= (kTeam ? (uint32_t)kCap : kSoloKeep) || round >= 7) break;
+        if (take_all || eq <= (kTeam ? (uint32_t)kCap : kSoloKeep) || round >= 8) break;
         if (by_key && wlo == whi) {
             by_key = false;
             ihi = (uint32_t)(L - 1);
@@ -3753,7 +3790,7 @@ topk_ragged_kernel(KArgs a) {
 // Calls in which no row is sampled (the policy's floor is above TOPK_L_MAX) and
 // whose rows may be split: a row's segments are the members of its team.  At
 // K = 8192 the decode batch ran its rows on one workgroup each in 60.9 us; in
-// teams of up to eight it takes 27.0.
+// teams of up to eight it takes 23.1 (27.2 with every coarse bin added).
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void
 topk_exact_kernel(KArgs a) {
     Smem &sm = g_sm;
