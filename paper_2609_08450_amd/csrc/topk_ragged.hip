@@ -8,9 +8,10 @@
 // longest first; blockIdx.x then indexes that order.
 //
 //   L <= K            segment 0 writes the direct layout (Section 2.1).
-//   not sampled       segment 0 runs exact coarse recovery alone
-//                     (eq:method:exact-init): coarse histogram pass, classify
-//                     pass, refinement.
+//   not sampled       the exact route (eq:method:exact-init): rounds of
+//                     histograms, then one selecting pass and refinement;
+//                     by one workgroup, by a team of them in calls without a
+//                     sampled row, or by the waves of a short row.
 //   sampled, 1 seg    Phase 1 (view histogram, eq:method:sample-hist and
 //                     eq:method:primary-threshold) -> Phase 2 (complete-row
 //                     certify + compact, eq:method:candidate-set) -> band or
