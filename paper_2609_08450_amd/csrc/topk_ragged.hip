@@ -3533,13 +3533,14 @@ topk_ragged_kernel(KArgs a) {
                 // segment stays for the finisher's verdict, to be a member of
                 // the row's team.  It goes by the entries reserved when it
                 // reserved its own, scaled to all of the row's reservations
-                // (one a wave, or one a segment), once a quarter of them are
-                // made: a segment's own count says little of its row where
+                // (one a wave, or one a segment), once an eighth of them are
+                // made (the tied codebook 57.4 us from a quarter, 53.6 from an
+                // eighth): a segment's own count says little of its row where
                 // hits come in runs (judged by it, the long split rows waited
                 // in every third segment, and took 1.2 us longer).
                 const uint32_t all = (wave_publish ? kWaves : 1u) * (uint32_t)P;
                 const uint32_t nres = (resv >> 20) + 1u, sum = (resv & (kReserved - 1u)) + own;
-                if (__builtin_expect((4u * nres >= all) &
+                if (__builtin_expect((8u * nres >= all) &
                                      ((sum * all > (uint32_t)a.cap * nres) |
                                       (sum * all * 8u < (uint32_t)a.K * 9u * nres)), 0))
                     inc |= 1ull << 48;
@@ -4431,8 +4432,16 @@ int launch_call(const float *scores, const int64_t *row_offsets, const int32_t *
         grid += extra;
     }
     if (pmax > 1 && a.l_samp_min > TOPK_L_MAX) {
-        // no row is sampled: teams of up to the resident workgroups
+        // No row is sampled: teams, whose members wait for each other, so every
+        // workgroup of the grid has to be resident at once.  Workgroups go to
+        // the dies in turn, so a grid within the resident workgroups is
+        // within each die's too; one that is larger, with only its live
+        // workgroups within them, filled some dies with members of every row
+        // (64 rows in 16 parts: 158 us, the bounded waits, against 23.1 in 8).
         a.seg_items = plan_slots(di.cus);
+        const int32_t most = plan_slots(di.cus) / n_rows;
+        a.pmax = most < 1 ? 1 : most > kMaxSplit ? kMaxSplit : most;
+        grid = (int64_t)n_rows * a.pmax;
         hipLaunchKernelGGL(topk_exact_kernel, dim3((unsigned)grid), dim3(kBlock), 0,
                            (hipStream_t)stream, a);
     } else if (a.order)

@@ -108,3 +108,18 @@ def test_failed_proposals_of_split_rows(topk, n, spin):  # noqa: F811
     assert st["exact_underfill"] > 0 and st["exact_overflow"] > 0 and st["reread"] > 0
     if spin:
         assert st["wait_fallback"] > 0
+
+
+@pytest.mark.parametrize("n", [33, 80, 150, 300])
+def test_every_member_is_resident(topk, n):  # noqa: F811
+    """Row counts between the powers of two, the long rows all on one die (every
+    eighth): no member waits in vain."""
+    rng = np.random.default_rng(79 + n)
+    K = 4400
+    lens = np.where(np.arange(n) % 8 == 0, rng.integers(60000, 131072, n),
+                    rng.integers(4401, 12000, n))
+    wl = _pack([W.decode_mixture_row(rng, int(L)) for L in lens], K, "one die")
+    for _ in range(3):
+        _, st = parity(topk, wl, per_k=True, where=f"{n} rows")
+        say(st)
+        assert st["wait_fallback"] == 0
