@@ -246,7 +246,8 @@ int topk_ragged_debug_cutoffs(uint32_t *out_cut, void *stream);
 
 /* Read-only ceiling of a call, for measurement: the work items topk_ragged
  * would launch for these rows and this K (the same split plan, per-K policy,
- * one workgroup for every row it does not split) stream every valid score
+ * one workgroup for every row it does not split, and for every row of a call
+ * without a sampled row, which topk_ragged runs by teams) stream every valid score
  * once with the same 16-byte loads and keep only the row's largest score.
  * Algorithmic bytes are the operator's own (one read of every valid score,
  * R_eq = 1 of Section 2.1, "Why long rows are expensive"), so the time of
