@@ -61,6 +61,7 @@ constexpr int kSegMin = 8192;               // shortest segment, elements
 constexpr uint32_t kMagic = 0x544F504Bu;    // workspace header tag
 constexpr int kSpinLimit = 1 << 15;         // polls before recomputing the view
 constexpr int kSpinMicros = 100;            // and the longest wait for the boundaries
+constexpr int kStartMicros = 4;             // and for the starts of a row's other segments
 constexpr size_t kHeaderBytes = 1024;
 constexpr size_t kRowStateBytes = 256;
 constexpr uintptr_t kWorkspaceAlign = 256; // 64-bit atomics and 16-byte header loads
@@ -134,6 +135,7 @@ struct RowState {
     uint64_t team;       // arrivals at the rounds' barriers | abandoned << 32
     uint64_t tslots;     // outputs reserved | kept entries reserved << 32
     uint32_t tbound;     // 2047 - the last coarse bin that every member has added
+    uint32_t started;    // segments that have started (counted with KArgs::count_starts)
 };
 static_assert(sizeof(RowState) <= kRowStateBytes, "row state fits its padding");
 
@@ -189,6 +191,9 @@ struct KArgs {
     int32_t cap;
     int32_t spin_limit; // polls of the boundary word before a segment builds the view itself
     uint32_t spin_ticks; // and the most constant-rate clock ticks it waits for them
+    uint32_t start_ticks; // and for the other segments' starts, before it may stay
+    uint32_t count_starts; // the grid is larger than the resident workgroups: a segment
+                           // stays for its row's verdict only once all of the row have started
 #ifdef TOPK_PHASE_TIMERS
     uint64_t *timers; // 32 words per workgroup, see PHASE_MARK
 #endif
@@ -3311,6 +3316,9 @@ topk_ragged_kernel(KArgs a) {
         // with a shared view any segment may wait for one dispatched after it.
         PHASE_MARK(a, 16);
         phase2_collect<kOrdered>(sm, a.scores, off, beg, end, [&]() {
+            if (!kOrdered && a.count_starts && split && tid == 0)
+                __hip_atomic_fetch_add(&rs->started, 1u, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
             bool have = false; // endpoints in sm
             if (coop) {
                 // (orders the clear of sm.hist before the additions: only a
@@ -3542,8 +3550,32 @@ topk_ragged_kernel(KArgs a) {
                 const uint32_t nres = (resv >> 20) + 1u, sum = (resv & (kReserved - 1u)) + own;
                 if (__builtin_expect((8u * nres >= all) &
                                      ((sum * all > (uint32_t)a.cap * nres) |
-                                      (sum * all * 8u < (uint32_t)a.K * 9u * nres)), 0))
-                    inc |= 1ull << 48;
+                                      (sum * all * 8u < (uint32_t)a.K * 9u * nres)), 0)) {
+                    // Workgroups go to the dies in turn, so with a grid within
+                    // the resident workgroups every segment has a slot.  A
+                    // larger one may give a die more live workgroups than it
+                    // holds (all of row r's when n_rows is a multiple of 8),
+                    // and segments that stay keep the slots that those they
+                    // wait for need: there they stay only once all of the row
+                    // have started, which they wait for a little (the first to
+                    // arrive have left).  Tied rows, each fourth of 12 of 500K
+                    // elements, each eighth of 48 of 262K, of 96 of 131K: 513,
+                    // 344 and 209 us when they stayed regardless (the waits ran
+                    // out), 418, 244 and 171 when none stayed, 64, 79 and 99 so.
+                    bool stays = true;
+                    if (a.count_starts && tid == 0) {
+                        uint32_t v = 0;
+                        const uint64_t t_wait = wall_clock64();
+                        for (int spin = 0; spin < a.spin_limit; spin++) {
+                            v = __hip_atomic_load(&rs->started, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+                            if (v == (uint32_t)P || wall_clock64() - t_wait > a.start_ticks) break;
+                            __builtin_amdgcn_s_sleep(1);
+                        }
+                        stays = v == (uint32_t)P;
+                    }
+                    if (stays) inc |= 1ull << 48;
+                }
             }
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
@@ -3630,7 +3662,11 @@ topk_ragged_kernel(KArgs a) {
             C0 = __builtin_amdgcn_readfirstlane(c0);
             amx = __builtin_amdgcn_readfirstlane(amx);
             incomplete = __builtin_amdgcn_readfirstlane(inc) != 0 || stored > (uint32_t)kFront;
-            if (tid == 0) sm.amax = amx; // for the general finish (barriers follow)
+            if (tid == 0) {
+                sm.amax = amx; // for the general finish (barriers follow)
+                if (!kOrdered && a.count_starts) // (every segment has arrived)
+                    __hip_atomic_store(&rs->started, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
             uint64_t left = 0; // thread 0: the route word before the verdict
             if constexpr (!kOrdered) {
                 if (__builtin_expect(waiting != 0u, 0)) {
@@ -4412,6 +4448,8 @@ int launch_call(const float *scores, const int64_t *row_offsets, const int32_t *
     a.cap = pol.cap;
     a.spin_limit = g_spin_limit > 0 ? g_spin_limit : kSpinLimit;
     a.spin_ticks = (uint32_t)((int64_t)kSpinMicros * di.clock_khz / 1000);
+    a.start_ticks = (uint32_t)((int64_t)kStartMicros * di.clock_khz / 1000);
+    a.count_starts = (int64_t)n_rows * pmax > plan_slots(di.cus);
     int64_t grid = (int64_t)n_rows * pmax;
     if (pmax == 1 && n_rows <= kOrderMaxRows) {
         // more rows than resident workgroups: longest rows first, so that

@@ -123,3 +123,22 @@ def test_every_member_is_resident(topk, n):  # noqa: F811
         _, st = parity(topk, wl, per_k=True, where=f"{n} rows")
         say(st)
         assert st["wait_fallback"] == 0
+
+
+@pytest.mark.parametrize("n,every,long,short", [
+    (12, 4, 500000, 4000), (24, 8, 262144, 4000), (48, 8, 262144, 30000),
+    (96, 8, 131072, 4000), (300, 8, 65536, 9000), (400, 8, 131072, 4000)])
+def test_segments_stay_for_running_ones_only(topk, n, every, long, short):  # noqa: F811
+    """Tied sampled rows whose grid is larger than the resident workgroups, the
+    long rows all on one or two dies: no staying segment waits in vain for one
+    that needs its slot."""
+    rng = np.random.default_rng(83 + n)
+    rows = []
+    for i in range(n):
+        book = np.sort(rng.standard_normal(4096))[:256]
+        rows.append(rng.choice(book, long if i % every == 0 else short))
+    wl = _pack(rows, 2048, "one die, tied")
+    for k in range(3):
+        _, st = parity(topk, wl, trace=False, where=f"{n} rows")
+        say(st)
+        assert k == 0 or st["wait_fallback"] == 0
