@@ -192,6 +192,7 @@ struct KArgs {
     int32_t spin_limit; // polls of the boundary word before a segment builds the view itself
     uint32_t spin_ticks; // and the most constant-rate clock ticks it waits for them
     uint32_t start_ticks; // and for the other segments' starts, before it may stay
+    uint32_t stay_above; // C(tau1) above which a row is taken for an overflowing one
     uint32_t count_starts; // the grid is larger than the resident workgroups: a segment
                            // stays for its row's verdict only once all of the row have started
 #ifdef TOPK_PHASE_TIMERS
@@ -3548,8 +3549,11 @@ topk_ragged_kernel(KArgs a) {
                 // in every third segment, and took 1.2 us longer).
                 const uint32_t all = (wave_publish ? kWaves : 1u) * (uint32_t)P;
                 const uint32_t nres = (resv >> 20) + 1u, sum = (resv & (kReserved - 1u)) + own;
+                // (both boundaries in one bin, as ties make them: C(tau0) is
+                // C(tau1); without this the tied codebook 81 us instead of 50)
+                const uint32_t most = sm.tau0 == sm.tau1 ? (uint32_t)a.cap : a.stay_above;
                 if (__builtin_expect((8u * nres >= all) &
-                                     ((sum * all > (uint32_t)a.cap * nres) |
+                                     ((sum * all > most * nres) |
                                       (sum * all * 8u < (uint32_t)a.K * 9u * nres)), 0)) {
                     // Workgroups go to the dies in turn, so with a grid within
                     // the resident workgroups every segment has a slot.  A
@@ -4448,6 +4452,13 @@ int launch_call(const float *scores, const int64_t *row_offsets, const int32_t *
     a.cap = pol.cap;
     a.spin_limit = g_spin_limit > 0 ? g_spin_limit : kSpinLimit;
     a.spin_ticks = (uint32_t)((int64_t)kSpinMicros * di.clock_khz / 1000);
+    // A row overflows when C(tau0) exceeds the capacity, and C(tau1) is about
+    // q1/q0 of that.  (With C(tau1) above the capacity itself, segments of many
+    // rows stayed in vain at K = 4096, where 5632 of 6144 are expected: the
+    // decode batch took 22.6 us there, and takes 20.2; without any that stay
+    // 20.0.  At most 2^20, so that the rule's products fit 32 bits.)
+    const int64_t above = (int64_t)pol.cap * a.q1 / a.q0;
+    a.stay_above = (uint32_t)(above < (int64_t)kReserved ? above : (int64_t)kReserved);
     a.start_ticks = (uint32_t)((int64_t)kStartMicros * di.clock_khz / 1000);
     a.count_starts = (int64_t)n_rows * pmax > plan_slots(di.cus);
     int64_t grid = (int64_t)n_rows * pmax;
