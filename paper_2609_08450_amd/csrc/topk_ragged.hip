@@ -135,7 +135,7 @@ struct RowState {
     uint64_t team;       // arrivals at the rounds' barriers | abandoned << 32
     uint64_t tslots;     // outputs reserved | kept entries reserved << 32
     uint32_t tbound;     // 2047 - the last coarse bin that every member has added
-    uint32_t started;    // segments that have started (counted with KArgs::count_starts)
+    uint32_t started;    // segments that have started (counted by the kCount instance)
 };
 static_assert(sizeof(RowState) <= kRowStateBytes, "row state fits its padding");
 
@@ -193,8 +193,6 @@ struct KArgs {
     uint32_t spin_ticks; // and the most constant-rate clock ticks it waits for them
     uint32_t start_ticks; // and for the other segments' starts, before it may stay
     uint32_t stay_above; // C(tau1) above which a row is taken for an overflowing one
-    uint32_t count_starts; // the grid is larger than the resident workgroups: a segment
-                           // stays for its row's verdict only once all of the row have started
 #ifdef TOPK_PHASE_TIMERS
     uint64_t *timers; // 32 words per workgroup, see PHASE_MARK
 #endif
@@ -3144,7 +3142,10 @@ __device__ __forceinline__ void finish_rare(const KArgs a, uint32_t C0, uint32_t
 // kOrdered: the call runs from the item table (a.order set).  Only such calls
 // take the split exact route; the other instance has none of its code (with
 // it, the decode batch measured 3 % slower although it never runs it).
-template <bool kOrdered>
+// kCount: the grid is larger than the resident workgroups, so a row's started
+// segments are counted (see the rule by which segments stay; with the count in
+// the one instance, a run-time choice, one row took 15.46 us instead of 15.31).
+template <bool kOrdered, bool kCount>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void
 topk_ragged_kernel(KArgs a) {
     Smem &sm = g_sm;
@@ -3317,7 +3318,7 @@ topk_ragged_kernel(KArgs a) {
         // with a shared view any segment may wait for one dispatched after it.
         PHASE_MARK(a, 16);
         phase2_collect<kOrdered>(sm, a.scores, off, beg, end, [&]() {
-            if (!kOrdered && a.count_starts && split && tid == 0)
+            if (kCount && split && tid == 0)
                 __hip_atomic_fetch_add(&rs->started, 1u, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
             bool have = false; // endpoints in sm
@@ -3567,7 +3568,7 @@ topk_ragged_kernel(KArgs a) {
                     // 344 and 209 us when they stayed regardless (the waits ran
                     // out), 418, 244 and 171 when none stayed, 64, 79 and 99 so.
                     bool stays = true;
-                    if (a.count_starts && tid == 0) {
+                    if (kCount && tid == 0) {
                         uint32_t v = 0;
                         const uint64_t t_wait = wall_clock64();
                         for (int spin = 0; spin < a.spin_limit; spin++) {
@@ -3668,7 +3669,7 @@ topk_ragged_kernel(KArgs a) {
             incomplete = __builtin_amdgcn_readfirstlane(inc) != 0 || stored > (uint32_t)kFront;
             if (tid == 0) {
                 sm.amax = amx; // for the general finish (barriers follow)
-                if (!kOrdered && a.count_starts) // (every segment has arrived)
+                if (kCount) // (every segment has arrived)
                     __hip_atomic_store(&rs->started, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             uint64_t left = 0; // thread 0: the route word before the verdict
@@ -4460,7 +4461,6 @@ int launch_call(const float *scores, const int64_t *row_offsets, const int32_t *
     const int64_t above = (int64_t)pol.cap * a.q1 / a.q0;
     a.stay_above = (uint32_t)(above < (int64_t)kReserved ? above : (int64_t)kReserved);
     a.start_ticks = (uint32_t)((int64_t)kStartMicros * di.clock_khz / 1000);
-    a.count_starts = (int64_t)n_rows * pmax > plan_slots(di.cus);
     int64_t grid = (int64_t)n_rows * pmax;
     if (pmax == 1 && n_rows <= kOrderMaxRows) {
         // more rows than resident workgroups: longest rows first, so that
@@ -4494,11 +4494,14 @@ int launch_call(const float *scores, const int64_t *row_offsets, const int32_t *
         hipLaunchKernelGGL(topk_exact_kernel, dim3((unsigned)grid), dim3(kBlock), 0,
                            (hipStream_t)stream, a);
     } else if (a.order)
-        hipLaunchKernelGGL(topk_ragged_kernel<true>, dim3((unsigned)grid), dim3(kBlock), 0,
+        hipLaunchKernelGGL((topk_ragged_kernel<true, false>), dim3((unsigned)grid), dim3(kBlock), 0,
+                           (hipStream_t)stream, a);
+    else if (pmax > 1 && grid > plan_slots(di.cus))
+        hipLaunchKernelGGL((topk_ragged_kernel<false, true>), dim3((unsigned)grid), dim3(kBlock), 0,
                            (hipStream_t)stream, a);
     else
-        hipLaunchKernelGGL(topk_ragged_kernel<false>, dim3((unsigned)grid), dim3(kBlock), 0,
-                           (hipStream_t)stream, a);
+        hipLaunchKernelGGL((topk_ragged_kernel<false, false>), dim3((unsigned)grid), dim3(kBlock),
+                           0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? TOPK_OK : TOPK_ELAUNCH;
 }
 
