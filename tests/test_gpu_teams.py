@@ -5,7 +5,9 @@ bounded wait the teams break up and the last member runs the row alone."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2609_08450_amd import workloads as W
+from tests.gpu_util import assert_same_selection, device_arrays
 from tests.test_gpu_parity import _reread_rows, parity, say, topk  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -110,15 +112,18 @@ def test_failed_proposals_of_split_rows(topk, n, spin):  # noqa: F811
         assert st["wait_fallback"] > 0
 
 
-@pytest.mark.parametrize("n", [33, 80, 150, 300])
-def test_every_member_is_resident(topk, n):  # noqa: F811
-    """Row counts between the powers of two, the long rows all on one die (every
-    eighth): no member waits in vain."""
-    rng = np.random.default_rng(79 + n)
-    K = 4400
+def _skewed(seed, n, K=4400):
+    rng = np.random.default_rng(seed)
     lens = np.where(np.arange(n) % 8 == 0, rng.integers(60000, 131072, n),
-                    rng.integers(4401, 12000, n))
-    wl = _pack([W.decode_mixture_row(rng, int(L)) for L in lens], K, "one die")
+                    rng.integers(K + 1, 12000, n))
+    return _pack([W.decode_mixture_row(rng, int(L)) for L in lens], K, "one die")
+
+
+@pytest.mark.parametrize("n", [33, 80, 150, 170, 256])
+def test_every_member_is_resident(topk, n):  # noqa: F811
+    """Row counts up to the last that forms teams, the long rows all on one die
+    (every eighth): no member waits in vain."""
+    wl = _skewed(79 + n, n)
     for _ in range(3):
         _, st = parity(topk, wl, per_k=True, where=f"{n} rows")
         say(st)
@@ -142,3 +147,119 @@ def test_segments_stay_for_running_ones_only(topk, n, every, long, short):  # no
         _, st = parity(topk, wl, trace=False, where=f"{n} rows")
         say(st)
         assert k == 0 or st["wait_fallback"] == 0
+
+
+@pytest.mark.parametrize("n", [257, 300, 512])
+def test_no_sampled_row_one_workgroup_each(topk, n):  # noqa: F811
+    """Calls of more rows than CUs without a sampled row: a workgroup a row."""
+    parity(topk, _skewed(89 + n, n), per_k=True, where=f"{n} rows")
+
+
+def _team_calls(seed):
+    """Calls whose rows are run by teams: without a sampled row, and tied ones
+    (n, K as of the call)."""
+    rng = np.random.default_rng(seed)
+    kinds = ("mixture", "equal", "one bin", "codes", "masked")
+    exact = _pack([_rows(rng, int(rng.integers(30000, 200000)), 8192, k) for k in kinds + kinds],
+                  8192, "no sampled row")
+    tied = []
+    for _ in range(12):
+        book = np.sort(rng.standard_normal(4096))[:256]
+        tied.append(rng.choice(book, int(rng.integers(70000, 200000))))
+    return exact, _pack(tied, 2048, "tied")
+
+
+def _check(wl, gi, gv, where):
+    oi, ov = oracle.topk_ragged(wl.scores, wl.row_offsets, wl.row_lengths, wl.K)
+    assert_same_selection(gi.cpu().numpy(), gv.cpu().numpy(), oi, ov, where=where)
+
+
+def _buffers(wl):
+    import torch
+
+    n = wl.n_rows
+    return (*device_arrays(wl), n, wl.K, torch.full((n, wl.K), -7, dtype=torch.int32, device="cuda"),
+            torch.full((n, wl.K), 7.0, device="cuda"))
+
+
+def test_team_state_across_calls(topk):  # noqa: F811
+    """One workspace for calls of both kinds in turn, with broken-up teams (one
+    poll per wait) between: each call finds the row state it needs."""
+    import torch
+
+    ws = topk.alloc_workspace(16, 8192)
+    calls = [(w, _buffers(w)) for s in (97, 101) for w in _team_calls(s)]
+    try:
+        for step, spin in enumerate([0, 0, 1, 0, 1, 1, 0]):
+            topk.debug_set_spin_limit(spin)
+            for w, b in calls:
+                b[5].fill_(-7)
+                topk.topk_ragged(*b, ws)
+                torch.cuda.synchronize()
+                _check(w, b[5], b[6], f"{w.name} step {step} spin {spin}")
+    finally:
+        topk.debug_set_spin_limit(0)
+    say(topk.read_stats(ws))
+
+
+@pytest.mark.parametrize("noalloc", [False, True], ids=["workspace", "noalloc"])
+def test_team_graph_replays(topk, noalloc):  # noqa: F811
+    """Both kinds captured in one graph, replayed with eager calls on the same
+    workspace between the replays."""
+    import torch
+
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ws = topk.alloc_workspace(16, 8192, torch.device("cuda", 0), stream)
+        calls = [(w, _buffers(w)) for w in _team_calls(103)]
+
+    def call(b):
+        if noalloc:
+            topk.topk_ragged_noalloc(*b, stream=stream)
+        else:
+            topk.topk_ragged(*b, ws, stream)
+
+    for _, b in calls:
+        call(b)
+    stream.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        for _, b in calls:
+            call(b)
+    for rep in range(3):
+        with torch.cuda.stream(stream):
+            for _, b in calls:
+                b[5].fill_(-7)
+            g.replay()
+        stream.synchronize()
+        for w, b in calls:
+            _check(w, b[5], b[6], f"{w.name} replay {rep}")
+            b[5].fill_(-7)
+        torch.cuda.synchronize()
+        for w, b in calls[::-1]:
+            call(b)
+        stream.synchronize()
+        for w, b in calls:
+            _check(w, b[5], b[6], f"{w.name} eager after replay {rep}")
+
+
+def test_teams_on_two_streams(topk):  # noqa: F811
+    """Two such calls at once, each with a stream and workspace of its own:
+    members of one may keep the other's from running until a wait ends."""
+    import torch
+
+    streams = (torch.cuda.Stream(), torch.cuda.Stream())
+    work = []
+    for k, st in enumerate(streams):
+        with torch.cuda.stream(st):
+            ws = topk.alloc_workspace(16, 8192, torch.device("cuda", 0), st)
+            work.append([(w, _buffers(w), ws, st) for w in _team_calls(107 + k)])
+    torch.cuda.synchronize()
+    for rep in range(4):
+        for pair in zip(*work):
+            for w, b, ws, st in pair:
+                topk.topk_ragged(*b, ws, st)
+    torch.cuda.synchronize()
+    for one in work:
+        for w, b, _, _ in one:
+            _check(w, b[5], b[6], f"{w.name} on two streams")
