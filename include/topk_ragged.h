@@ -102,10 +102,14 @@ typedef struct topk_ragged_policy {
 typedef struct topk_ragged_stats {
     uint64_t route[6];     /* indexed by TOPK_ROUTE_* (flag stripped) */
     uint64_t reread;       /* rows that took the re-read fallback */
-    uint64_t wait_fallback;/* split segments that stopped waiting: for the
-                              boundaries (they recompute the view locally),
-                              or for tau_star of the split exact route (the
-                              last segment then runs the row's exact route) */
+    uint64_t wait_fallback;/* segments that stopped waiting: for the
+                              boundaries (they recompute the view locally);
+                              for tau_star of the split exact route, for the
+                              verdict of the row they stayed for, or for the
+                              other members of a row's team, in calls without a
+                              sampled row too (the last segment then runs the
+                              row's exact route; after a verdict that the row
+                              takes another route nothing falls back) */
     uint64_t errors;       /* rejected on the device: one per call with a bad
                               workspace, one per row longer than TOPK_L_MAX */
 } topk_ragged_stats;
@@ -245,13 +249,15 @@ int topk_ragged_debug_coarse(const float *x, int64_t n, uint16_t *out_c, void *s
 int topk_ragged_debug_cutoffs(uint32_t *out_cut, void *stream);
 
 /* Read-only ceiling of a call, for measurement: the work items topk_ragged
- * would launch for these rows and this K (the same split plan, per-K policy,
+ * would launch for these rows and this K (the same split plan and per-K policy;
  * one workgroup for every row it does not split, and for every row of a call
- * without a sampled row, which topk_ragged runs by teams) stream every valid score
- * once with the same 16-byte loads and keep only the row's largest score.
- * Algorithmic bytes are the operator's own (one read of every valid score,
- * R_eq = 1 of Section 2.1, "Why long rows are expensive"), so the time of
- * this call bounds what the selector can reach in that geometry.  out_max: device, uint32
+ * without a sampled row) stream every valid score once with the same 16-byte
+ * loads and keep only the row's largest score.  Algorithmic bytes are the
+ * operator's own (one read of every valid score, R_eq = 1 of Section 2.1, "Why
+ * long rows are expensive"), so the time of this call bounds what the selector
+ * can reach in that geometry on sampled rows.  It is no bound where the
+ * selector's geometry is another: rows of a call without a sampled row (run by
+ * teams), and short rows (several to a workgroup).  out_max: device, uint32
  * [n_rows], caller-owned, zeroed by the caller; receives the order-preserving
  * key of each row's largest score (0 for an empty row).  workspace: an
  * initialised workspace for at least n_rows rows (as for topk_ragged), whose
@@ -262,10 +268,12 @@ int topk_ragged_debug_read_ceiling(const float *scores, const int64_t *row_offse
                                    const int32_t *row_lengths, int32_t n_rows, int32_t K,
                                    uint32_t *out_max, void *workspace, void *stream);
 
-/* For tests of the split-row wait (Section 4.5 mapping): the number of polls a
- * segment makes for segment 0's published boundaries before it builds the
- * view itself (counted in topk_ragged_stats.wait_fallback), for the calls
- * launched after it; 0 restores the default.  Results do not depend on it.
+/* For tests of the bounded waits (Section 4.5 mapping): the number of polls a
+ * segment makes in each of them (for the published boundaries, for tau_star of
+ * the split exact route, for the verdict of a row it stayed for and the starts of
+ * that row's segments, for the other members of a team) before it goes on without
+ * (topk_ragged_stats.wait_fallback counts all of these but the starts), for the
+ * calls launched after it; 0 restores the default.  Results do not depend on it.
  * Process-wide, not synchronised with concurrent calls.  Returns TOPK_OK, or
  * TOPK_EINVAL for a negative count. */
 int topk_ragged_debug_set_spin_limit(int32_t polls);

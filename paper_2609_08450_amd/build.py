@@ -19,9 +19,12 @@ FLAGS = [
     # rewrite only adds instructions and waits for returned values at once
     "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
     # hoisting out of the machine loops only lengthens live ranges in kernels
-    # of this size: without it the decode instance takes 91 vector registers
-    # instead of 105, the decode batch 15.82 us (15.87), the captured decode
-    # step 105.4 (106.8), 256 rows 24.1 (24.2); chunked prefill 431.6 (430.6)
+    # of this size: without it the instance for planned splits takes 96 vector
+    # registers instead of 112, the one for item tables 91 instead of 98, the
+    # exact kernel 96 instead of 113 (when it was left out: the decode batch
+    # 15.82 us instead of 15.87, the captured decode step 105.4 instead of
+    # 106.8, 256 rows 24.1 instead of 24.2, chunked prefill 431.6 instead of
+    # 430.6)
     "-mllvm", "-disable-machine-licm",
     "-Wall",
 ]

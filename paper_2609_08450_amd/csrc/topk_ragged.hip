@@ -126,9 +126,13 @@ struct RowState {
     // finisher's tau_star, classify their own ranges and arrive again):
     alignas(128) uint32_t ocnt; // outputs reserved (entries with c < tau_star)
     uint32_t qcnt;       // kept entries (c == tau_star) reserved in the candidate buffer
-    uint32_t arrive2;    // second arrivals
+    uint32_t arrive2;    // second arrivals (a team's: members that have left it,
+                         // with those that gave up before the verdict)
     uint64_t xtau;       // the route word: tau_star | arrivals expected << 11 |
-                         // abandoned << 30 | 1 << 31 | |Q0| << 32 | |E0| << 48
+                         // abandoned << 30 | 1 << 31 | |Q0| << 32 | |E0| << 48;
+                         // in a call without an item table the verdict: members
+                         // << 11 | no team << 30 | 1 << 31 | segments that left
+                         // without joining << 32
     uint64_t xmask;      // segments that stopped waiting
     // The team exact route (every member of a row's team adds a histogram,
     // waits for the others, and selects in its own range):
@@ -392,7 +396,7 @@ __device__ __forceinline__ void wave_find_bins2(const uint32_t *hist, uint32_t i
     b1 = ok1 ? (uint32_t)(own1 * 32 + l1) : (uint32_t)kBins;
 }
 
-__device__ __forceinline__ void wave_find(const uint32_t *hist, uint32_t k0, uint32_t k1, int nk, Find *out) {
+__device__ __forceinline__ void wave_find(const uint32_t *hist, uint32_t k, Find *out) {
     const int lane = lane_id();
     const uint4 *h4 = reinterpret_cast<const uint4 *>(hist + lane * 32);
     uint32_t tot = 0;
@@ -403,23 +407,25 @@ __device__ __forceinline__ void wave_find(const uint32_t *hist, uint32_t k0, uin
     }
     const uint32_t incl = wave_incl_scan(tot);
     const uint32_t total = __builtin_amdgcn_readlane(incl, 63);
-    wave_find_level2(hist, incl, tot, total, k0, &out[0]);
-    if (nk > 1) wave_find_level2(hist, incl, tot, total, k1, &out[1]);
+    wave_find_level2(hist, incl, tot, total, k, out);
 }
 
 // Sums of the 64 groups of 32 bins of a 2048-bin histogram into out[64], by
-// the whole block: thread t adds bins [4 t, 4 t + 4), then each group of 8
-// lanes is summed with DPP row shifts (lane 8 g + 7 holds group g's sum).
-// Needs the histogram complete (caller's barrier); out is complete after the
-// next barrier.
+// the whole block: h holds the thread's bins [4 tid, 4 tid + 4), and each group
+// of 8 lanes is summed with DPP row shifts (lane 8 g + 7 holds group g's sum).
+// out is complete after the next barrier.
 static_assert(kBlock * 4 == kBins, "group_sums: one uint4 of bins per thread");
-__device__ __forceinline__ void group_sums(const uint32_t *hist, uint32_t *out) {
-    const uint4 h = reinterpret_cast<const uint4 *>(hist)[threadIdx.x];
+__device__ __forceinline__ void group_sums_of(const uint4 &h, uint32_t *out) {
     uint32_t v = h.x + h.y + h.z + h.w;
     v += __builtin_amdgcn_update_dpp(0u, v, 0x111, 0xf, 0xf, false); // row_shr:1
     v += __builtin_amdgcn_update_dpp(0u, v, 0x112, 0xf, 0xf, false); // row_shr:2
     v += __builtin_amdgcn_update_dpp(0u, v, 0x114, 0xf, 0xf, false); // row_shr:4
     if ((threadIdx.x & 7u) == 7u) out[threadIdx.x >> 3] = v;
+}
+
+// The same of a complete histogram (caller's barrier).
+__device__ __forceinline__ void group_sums(const uint32_t *hist, uint32_t *out) {
+    group_sums_of(reinterpret_cast<const uint4 *>(hist)[threadIdx.x], out);
 }
 
 // ------------------------------------------------- shared state ----
@@ -575,15 +581,14 @@ __device__ __forceinline__ bool in_window(int32_t i, int32_t lo, int32_t hi) {
     return i >= lo && i < hi;
 }
 
-// Appends every element of the range whose ascending key u satisfies
-// lo_key <= u < hi_key to the LDS frontier (index, kappa32); sm.cnt counts all
-// of them even past the capacity.  Phase 2 of Section 4.3 with hi_key = ~0
-// (plus the top key itself, see below); the band of eq:method:rescue-band
-// with [cut1, cut0).
+// Appends every element of the range whose ascending key is at least lo_key to
+// the LDS frontier (index, kappa32); sm.cnt counts all of them even past the
+// capacity.  The certified tail of Section 4.3 (lo_key = cut0), or that of the
+// band of eq:method:rescue-band (cut1), of a row whose stored entries are
+// incomplete.
 template <bool kNT>
 __device__ __forceinline__ void collect_range(Smem &sm, const float *scores, int64_t off, int32_t beg,
-                              int32_t end, uint32_t lo_key, uint32_t hi_key, bool hi_inclusive,
-                              uint32_t cap) {
+                              int32_t end, uint32_t lo_key, uint32_t cap) {
     stream_row<kNT>(scores, off, beg, end, [&](const f4 *x, const int32_t *i0, int32_t lo,
                                                int32_t hi, bool, int32_t mv) {
         uint64_t mask = 0; // one bit per element of the chunk (kVec * 4 <= 64)
@@ -592,8 +597,7 @@ __device__ __forceinline__ void collect_range(Smem &sm, const float *scores, int
 #pragma unroll
             for (int c = 0; c < 4; c++) {
                 const uint32_t u = asc_key(fbits(x[m][c]));
-                const bool ok = u >= lo_key && (hi_inclusive ? u <= hi_key : u < hi_key) &&
-                                in_window(i0[m] + c, lo, hi);
+                const bool ok = u >= lo_key && in_window(i0[m] + c, lo, hi);
                 mask |= (ok ? 1ull : 0ull) << (m * 4 + c);
             }
         }
@@ -1319,16 +1323,6 @@ __device__ __forceinline__ uint32_t raw_bin(float x) {
     return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)x) >> 5;
 }
 __device__ __forceinline__ uint32_t raw_bin_of(uint32_t c) { return c < 1024u ? 1023u - c : c; }
-
-// The thread's four bins of a histogram (4 tid ..) summed into 64 group sums
-// of 32 bins each (complete after the next barrier).
-__device__ __forceinline__ void group_sums_of(const uint4 &h, uint32_t *out) {
-    uint32_t v = h.x + h.y + h.z + h.w;
-    v += __builtin_amdgcn_update_dpp(0u, v, 0x111, 0xf, 0xf, false); // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0u, v, 0x112, 0xf, 0xf, false); // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0u, v, 0x114, 0xf, 0xf, false); // row_shr:4
-    if ((threadIdx.x & 7u) == 7u) out[threadIdx.x >> 3] = v;
-}
 
 // min{b : H(b) >= k} with its counts, by every wave on its own; groups: the
 // 64 group sums.  raw: hist and groups are in raw FP16 order.
@@ -2104,7 +2098,7 @@ __device__ __forceinline__ void finish_row(const KArgs a, Smem &sm, int r, int64
         if (incomplete) {
             if (threadIdx.x == 0) sm.cnt = 0;
             __syncthreads();
-            collect_range<false>(sm, a.scores, off, 0, (int32_t)L, kmin, 0xFFFFFFFFu, true, cap);
+            collect_range<false>(sm, a.scores, off, 0, (int32_t)L, kmin, cap);
             __syncthreads();
             f_seg = false;
             f_raw = false;
@@ -2281,8 +2275,10 @@ __device__ __forceinline__ bool finish_fast(const KArgs a, Smem &sm, int r, int6
 // ----------------------------------------------------------- kernel ----
 
 // Leaves a split row's state zeroed for the next call (graph replays).
-// x: also the split exact route's fields (written only in calls run from
-// the item table).
+// x: also the fields of the split exact route (calls run from the item table)
+// and of a verdict (the others): needed after either, and after a verdict of "no
+// team" by whoever is the last to touch the route word.  A team's last member
+// has zeroed the team's own fields before (team_reset), arrive2 among them.
 __device__ __forceinline__ void reset_row_state(RowState *rs, bool x = true) {
     __hip_atomic_store(&rs->counts, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&rs->sa, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -3755,7 +3751,7 @@ topk_ragged_kernel(KArgs a) {
                 __syncthreads();
                 bool dist = false;
                 if (have_hist) {
-                    if (tid < 64) wave_find(sm.hist, K, 0, 1, sm.find);
+                    if (tid < 64) wave_find(sm.hist, K, sm.find);
                     __syncthreads();
                     dist = sm.find[0].eq <= cap;
                 }
@@ -4165,15 +4161,16 @@ __global__ void debug_cutoff_kernel(uint32_t *out) {
 
 // ------------------------------------------------------------- host ----
 
-// Read-only ceiling of a call: the same work items as topk_ragged_kernel
-// (the same item table or split plan; every other row is read by one
-// workgroup) stream every valid score once with the same
+// Read-only ceiling of a call: the work items of topk_ragged_kernel for its
+// sampled rows (the same item table or split plan; every other row is read by
+// one workgroup of its own, where the selector may use a team, or put several
+// short rows on one) stream every valid score once with the same
 // loads (two chunks of 16-byte non-temporal loads in flight per thread) and
 // keep only the largest ascending key, which one atomic per workgroup adds
 // into out_max[r] (atomics on one address queue: one per wave made the
 // long-split batch's ceiling 1.5 times slower than the selector itself).  It
-// measures what reading the call's rows costs in this launch geometry, with
-// none of the selection.
+// measures what reading the call's sampled rows costs in this launch geometry,
+// with none of the selection.
 __global__ __launch_bounds__(kBlock) void read_ceiling_kernel(KArgs a, uint32_t *out_max) {
     __shared__ int64_t lsum[kWaves];
     __shared__ uint32_t wmax[kWaves];
@@ -4487,6 +4484,8 @@ int launch_call(const float *scores, const int64_t *row_offsets, const int32_t *
         // within each die's too; one that is larger, with only its live
         // workgroups within them, filled some dies with members of every row
         // (64 rows in 16 parts: 158 us, the bounded waits, against 23.1 in 8).
+        // With more rows than CUs that is one workgroup a row, as without
+        // teams.
         a.seg_items = plan_slots(di.cus);
         const int32_t most = plan_slots(di.cus) / n_rows;
         a.pmax = most < 1 ? 1 : most > kMaxSplit ? kMaxSplit : most;
